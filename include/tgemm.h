@@ -455,7 +455,11 @@ int tgemm_load_tuning_db(const char* db_path);
 uint64_t tgemm_schedule_space_hash(void);
 
 /* Schedule the current policy would pick for a dense problem (row strides K
- * and N, 16-byte aligned bases).  Host-only. */
+ * and N, 16-byte aligned bases).  Under the built-in rule tgemm and
+ * tgemm_noalloc run float32 problems of few tiles on register tiles, which are
+ * no schedules of the table; what is reported here is the schedule that serves
+ * such a problem where those tiles do not (operands off 4-byte alignment or
+ * row strides past their reach).  Host-only. */
 int tgemm_select_schedule(int64_t M, int64_t N, int64_t K, int dtype,
                           int* schedule_id, int* group_m, int* xcd_remap);
 

@@ -13,6 +13,7 @@
 #include <string>
 
 #include "../../include/tgemm.h"
+#include "gemm_reg.h"
 #include "kargs.h"
 #include "registry.h"
 #include "select.h"
@@ -155,6 +156,20 @@ int run_gemm(int id, int64_t M, int64_t N, int64_t K, float alpha, const void* A
     return launch_gemm(d, a, stream) == hipSuccess ? TGEMM_SUCCESS : TGEMM_LAUNCH_FAILED;
 }
 
+// A float32 problem as the selection chose: on a register tile where the rule
+// names one that serves the operands, else on the schedule.
+int run_choice(const Choice& ch, int64_t M, int64_t N, int64_t K, float alpha, const void* A, int64_t lda,
+               const void* B, int64_t ldb, float beta, float* C, int64_t ldc, int dtype, hipStream_t stream)
+{
+    if (ch.reg >= 0) {
+        const int rc = run_reg(ch.reg, dtype, M, N, K, 1, alpha, static_cast<const float*>(A), true, lda, 0,
+                               static_cast<const float*>(B), false, ldb, 0, beta, C, ldc, 0, ch.group_m,
+                               ch.xcd_remap, stream);
+        if (rc != TGEMM_NOT_SUPPORTED) return rc;
+    }
+    return run_gemm(ch.id, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, ch.group_m, ch.xcd_remap, stream);
+}
+
 }  // namespace tg
 
 // ------------------------------------------------------------------- C ABI
@@ -197,8 +212,7 @@ int tgemm(int64_t M, int64_t N, int64_t K, float alpha, const void* A, int64_t l
             rc = run_scaled(M, N, K, alpha, A, lda, nullptr, B, ldb, nullptr, beta, C, ldc, dtype,
                             ch.id, ch.group_m, ch.xcd_remap, s);
         else
-            rc = run_gemm(ch.id, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, ch.group_m,
-                          ch.xcd_remap, s);
+            rc = run_choice(ch, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, dtype, s);
         // a packed schedule whose workspace would have to grow under capture, or an
         // in-place one whose rows lie past the reach of its buffer offsets: use the
         // rule's schedule without packing instead

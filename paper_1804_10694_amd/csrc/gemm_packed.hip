@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "../../include/tgemm.h"
+#include "gemm_reg.h"
 #include "kargs.h"
 #include "registry.h"
 #include "select.h"
@@ -32,6 +33,8 @@ int run_gemm(int id, int64_t M, int64_t N, int64_t K, float alpha, const void* A
 int run_scaled(int64_t M, int64_t N, int64_t K, float alpha, const void* A, int64_t lda,
                const float* sA, const void* B, int64_t ldb, const float* sB, float beta, float* C,
                int64_t ldc, int dtype, int id, int group_m, int xcd_remap, hipStream_t s);
+int run_choice(const Choice& ch, int64_t M, int64_t N, int64_t K, float alpha, const void* A, int64_t lda,
+               const void* B, int64_t ldb, float beta, float* C, int64_t ldc, int dtype, hipStream_t stream);
 
 // ------------------------------------------------------------------ kernels
 // Groups of 8 k are numbered row by row; fewer than 2^32 of them (checked on
@@ -685,7 +688,7 @@ extern "C" int tgemm_noalloc(int64_t M, int64_t N, int64_t K, float alpha, const
         if (scaled)
             return run_scaled(M, N, K, alpha, A, lda, nullptr, B, ldb, nullptr, beta, C, ldc, dtype, ch.id,
                               ch.group_m, ch.xcd_remap, s);
-        rc = run_gemm(ch.id, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, ch.group_m, ch.xcd_remap, s);
+        rc = run_choice(ch, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, dtype, s);
         // an in-place schedule whose rows lie past the reach of its buffer offsets
         if (rc != TGEMM_NOT_SUPPORTED || !schedule(ch.id).inplace) return rc;
         if ((rc = direct_schedule(M, N, K, dtype, vok, &ch)) != TGEMM_SUCCESS) return rc;
@@ -694,6 +697,8 @@ extern "C" int tgemm_noalloc(int64_t M, int64_t N, int64_t K, float alpha, const
     if (!packed_k_ok(K, dtype)) return TGEMM_NOT_SUPPORTED;
     if (packed_workspace_bytes(M, N, K, dtype) > (size_t)TGEMM_NOALLOC_SCRATCH_BYTES)
         return TGEMM_SCRATCH_TOO_SMALL;
+    if (ch.reg >= 0 && reg_serves(A, true, lda, B, false, ldb))  // few tiles: no workspace after all
+        return run_choice(ch, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, dtype, s);
     void* ws = nullptr;
     if ((rc = scratch_address(&ws)) != TGEMM_SUCCESS) return rc;
     // a stream-K form needs counters the library allocates: its row runs instead,

@@ -12,6 +12,7 @@
 #include <tuple>
 
 #include "../../include/tgemm.h"
+#include "gemm_reg.h"
 #include "registry.h"
 
 namespace tg {
@@ -152,10 +153,12 @@ int direct_schedule(int64_t M, int64_t N, int64_t K, int dtype, bool vec_allowed
     out->id = id;
     out->group_m = 8;
     out->xcd_remap = 1;
+    out->reg = -1;
     return TGEMM_SUCCESS;
 }
 
-int default_schedule(int64_t M, int64_t N, int64_t K, int dtype, bool vec_allowed, Choice* out)
+// The schedule of the table for these sizes.
+static int table_rule(int64_t M, int64_t N, int64_t K, int dtype, bool vec_allowed, Choice* out)
 {
     auto tiles = [&](int bm, int bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
     auto take = [&](int id) {
@@ -291,6 +294,13 @@ int default_schedule(int64_t M, int64_t N, int64_t K, int dtype, bool vec_allowe
     return direct_schedule(M, N, K, dtype, vec_allowed, out);
 }
 
+int default_schedule(int64_t M, int64_t N, int64_t K, int dtype, bool vec_allowed, Choice* out)
+{
+    const int rc = table_rule(M, N, K, dtype, vec_allowed, out);
+    if (rc == TGEMM_SUCCESS) out->reg = reg_choice(M, N, K, dtype);
+    return rc;
+}
+
 int select_schedule(int64_t M, int64_t N, int64_t K, int dtype, bool vec_allowed, Choice* out,
                     bool may_run_model)
 {
@@ -306,6 +316,7 @@ int select_schedule(int64_t M, int64_t N, int64_t K, int dtype, bool vec_allowed
                 out->id = force_id;
                 out->group_m = 8;
                 out->xcd_remap = 1;
+                out->reg = -1;
                 return TGEMM_SUCCESS;
             }
         } else if (pol == POLICY_TUNED) {

@@ -10,6 +10,8 @@ struct Choice {
     int id;
     int group_m;
     int xcd_remap;
+    int reg = -1;  // register tile that runs the problem instead of the schedule where it can
+                   // (set by the built-in rule only: the table's ids name LDS-pipeline schedules)
 };
 
 // Picks a schedule for the current policy; vec_allowed says whether the
