@@ -39,6 +39,7 @@
 #include <vector>
 
 #include "../../include/tgemm.h"
+#include "gemm_reg.h"
 #include "kargs.h"
 #include "registry.h"
 #include "tile_f32x3.h"
@@ -913,6 +914,12 @@ int strided_run(int64_t count, int64_t M, int64_t N, int64_t K, float alpha, con
         if (M <= 16 && N <= 16) hipLaunchKernelGGL(small_batched_kernel<16>, dim3(blocks), dim3(256), 0, s, sa);
         else hipLaunchKernelGGL(small_batched_kernel<32>, dim3(blocks), dim3(256), 0, s, sa);
         return hipGetLastError() == hipSuccess ? TGEMM_SUCCESS : TGEMM_LAUNCH_FAILED;
+    }
+    if (reg_strided_pays(M, N, K, count, dtype, 0) && alpha != 0.f && K > 0) {
+        if ((rc = ensure_device(s)) != TGEMM_SUCCESS) return rc;
+        rc = run_reg(reg_best_tile(M, N, K, count, dtype), dtype, M, N, K, count, alpha, static_cast<const float*>(A),
+                     true, lda, sA, static_cast<const float*>(B), false, ldb, sB, beta, C, ldc, sC, 8, 1, s);
+        if (rc != TGEMM_NOT_SUPPORTED) return rc;
     }
     const std::vector<uint64_t> key = {0x5354524944454431ull, (uint64_t)count, (uint64_t)dtype,
                                        (uint64_t)M, (uint64_t)N, (uint64_t)K, fbits(alpha), fbits(beta),

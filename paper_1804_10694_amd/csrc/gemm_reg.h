@@ -10,6 +10,9 @@ namespace tg {
 int reg_choice(int64_t M, int64_t N, int64_t K, int dtype);
 // The fastest register tile for a batch, whether or not one pays.
 int reg_best_tile(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype);
+// Whether register tiles pay for `batch` products at fixed strides, where the
+// other way copies `copied` elements into another order first.
+bool reg_strided_pays(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, int64_t copied);
 // Whether the tiles' 32-bit offsets reach operands of these strides.  ak / bk:
 // A / B has K contiguous (its stride is between rows; otherwise between k).
 bool reg_serves(const void* A, bool ak, int64_t lda, const void* B, bool bk, int64_t ldb);

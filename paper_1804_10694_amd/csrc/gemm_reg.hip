@@ -108,6 +108,23 @@ int reg_choice(int64_t M, int64_t N, int64_t K, int dtype)
     return t64 <= most ? reg_best_tile(M, N, K, 1, dtype) : -1;
 }
 
+// Batches.  Nothing copied: up to 1100 tiles of 64 x 64 with K from 128, or 256
+// of any K (MI355X, microseconds, against the grouped launch: f32 16 x 256^3
+// 11.7 / 25.4, 64 x 256^3 27.4 / 29.2, 4 x 1024^3 74 / 82, x3 19 / 22 and 44 / 58
+// for the last two; past the line f32 256 x 256^3 93 / 81 and 1000 x 64^3 15.2 /
+// 13.8).  Otherwise the copies cost 1.33 us a megabyte and the larger tiles
+// save 1.0 us (f32) or 1.43 us (x3) a gigaflop: f32 64 x 256^3 26 / 75, 2 x 4096^2
+// x 2048 1052 / 1157, x3 4 x 2048^2 x 1024 158 / 208; past it x3 2 x 4096^2 x 2048
+// 659 / 614.  Products of at most 32 x 32 have a kernel of their own.
+bool reg_strided_pays(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, int64_t copied)
+{
+    if (std::max(M, N) <= 32) return false;
+    if (copied > 0)
+        return 2e-9 * (double)M * N * K * batch * (dtype == TGEMM_F32 ? 1.0 : 1.43) < 4e-6 * (double)copied * 1.33;
+    const int64_t t64 = ((M + 63) / 64) * ((N + 63) / 64) * batch;
+    return t64 <= (K < 128 ? 256 : 1100);
+}
+
 // Every offset inside a tile's chunk fits in 31 bits and floats are 4-byte
 // aligned: K contiguous, 64 rows; row contiguous, 16 k (and 64 floats).
 bool reg_serves(const void* A, bool ak, int64_t lda, const void* B, bool bk, int64_t ldb)

@@ -64,3 +64,42 @@ def test_beta_zero_does_not_read_c_and_infinities_stay_in_their_rows(tg):
     ref = A[rows].double() @ B.double()
     np.testing.assert_array_equal(C.cpu()[rows].double().numpy(), ref.numpy())
     assert not torch.isfinite(C.cpu()[3][B[7] != 0]).any()
+
+
+# labels: 9, 8 batch; 0, 5 rows; 2, 6 columns; 1, 3 contracted.  Every order of A, B and C that keeps one
+# of its modes contiguous is read (or written) in place; the others go through copies
+EXT = {9: 3, 8: 2, 0: 40, 5: 3, 2: 37, 6: 2, 1: 35, 3: 4}
+ORDERS = [([9, 0, 1], [9, 1, 2], [9, 0, 2]), ([1, 9, 0], [9, 2, 1], [9, 0, 2]), ([9, 1, 0], [1, 9, 2], [0, 9, 2]),
+          ([0, 9, 1], [2, 9, 1], [9, 2, 0]), ([1, 0, 9], [9, 1, 2], [9, 0, 2]), ([9, 0, 1], [9, 1, 2], [2, 0, 9]),
+          ([8, 9, 0, 5, 1, 3], [1, 3, 8, 9, 2], [8, 9, 0, 5, 2]), ([9, 8, 0, 5, 1], [8, 9, 1, 2, 6], [8, 9, 0, 5, 2, 6]),
+          ([1, 3, 0, 5], [2, 6, 1, 3], [0, 5, 2, 6]), ([0, 5, 3, 1], [2, 1, 3], [2, 0, 5]), ([1, 0], [1, 2], [0, 2]),
+          ([0, 1], [2, 1], [2, 0]), ([9, 0], [9, 2], [9, 0, 2]), ([9, 1], [9, 2, 1], [9, 2]),
+          ([1, 9, 0], [1, 9], [9, 0])]
+
+
+@pytest.mark.parametrize("order", ORDERS, ids=lambda o: "_".join("".join(map(str, m)) for m in o))
+@pytest.mark.parametrize("dtype", ["f32", "x3"])
+def test_contraction_in_any_order_exact(tg, dtype, order):
+    from oracle import contract as OT
+    ma, mb, mc = order
+    g = torch.Generator().manual_seed(17)
+    A, B, C0 = (torch.randint(-8, 9, [EXT[m] for m in o], generator=g).float() for o in (ma, mb, mc))
+    for alpha, beta in ((1.0, 0.0), (1.5, 0.5)):
+        C = torch.full_like(C0, float("nan")) if beta == 0 else C0.clone()
+        C = C.to(DEV)
+        tg.contract(A.to(DEV), ma, B.to(DEV), mb, C, mc, alpha, beta, dtype)
+        np.testing.assert_array_equal(C.cpu().numpy().astype(np.float64),
+                                      OT.contract(A, ma, B, mb, mc, C0, alpha, beta))
+
+
+@pytest.mark.parametrize("dims", [(256, 64, 64, 65), (16, 130, 200, 129), (1101, 33, 20, 128), (1100, 40, 64, 128)])
+@pytest.mark.parametrize("dtype", ["f32", "x3"])
+def test_strided_batch_exact(tg, dtype, dims):
+    # on both sides of the tile counts where register tiles take a batch
+    P, M, N, K = dims
+    g = torch.Generator().manual_seed(18)
+    A, B, C0 = (torch.randint(-8, 9, d, generator=g).float() for d in ((P, M, K), (P, K, N), (P, M, N)))
+    C = C0.to(DEV)
+    tg.gemm_batched_strided(A.to(DEV), B.to(DEV), C, 1.0, 1.0, dtype)
+    ref = torch.bmm(A.double(), B.double()) + C0.double()
+    np.testing.assert_array_equal(C.cpu().double().numpy(), ref.numpy())
