@@ -183,6 +183,104 @@ struct ConvRowsA {
     }
 };
 
+// A steps of the kernel that takes turns (TCfg, x3): X split beforehand into
+// units of eight channels' high parts, then their low parts, so the four units
+// of a pixel's step are one run of 64 bytes (within a tap).  Unit u of a row
+// is channels 8 (u % 2) .. of the step, high (u < 2) or low.  Steps are issued
+// in order, so the tap and channel advance by addition; a division per unit and
+// step would take longer than the slot its issue has.
+template <class CF, int FR>
+struct ConvStepsA {
+    using Geom = ConvGeom;
+    using SP = StepPack<CF::MODE>;
+    static constexpr int NI = CF::BM * SP::UK / 64 / CF::NW;
+    static constexpr int LOADS = NI;
+    static constexpr uint32_t OOB = 0xfffffff0u;  // at or past the end of any X here (below 2^32 - 31 bytes)
+
+    __amdgpu_buffer_rsrc_t r;
+    int wave, H, W, C, half, k;      // k: first of the next step, this lane's first unit
+    int taps;                        // taps left from the current one on (0: past K)
+    int ci, dy, dx;                  // channel and tap of k
+    uint32_t at[NI];                 // byte offset of (output pixel, channel 0), the unit's array added
+    int py[NI], px[NI];              // output pixel's y (far outside past M) and x
+
+    __device__ __forceinline__ void init(const PackedArgs& a, int m0, int lane, int wave_, const Geom& g)
+    {
+        static_assert(CF::MODE == MODE_X3 && CF::BK == 16, "steps of two units of eight channels");
+        wave = wave_;
+        H = g.H;
+        W = g.W;
+        C = g.C;
+        const int R = FR > 0 ? FR : g.R;
+        half = R / 2;
+        r = make_rsrc(a.A, (int)((uint32_t)a.M * (uint32_t)C * 4u));
+        // the lane's unit is the same in every instruction: 16 rows further the
+        // swizzle of pk_slot repeats
+        const int u = ((lane % SP::UK) ^ (lane / 16)) & (SP::UK - 1);
+        const int first = 8 * (u & 1);
+        const int tap = first / C;  // C is 8 or more
+        ci = first - tap * C;
+        dy = -half + tap / R;
+        dx = -half + tap % R;
+        taps = R * R - tap;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const int m = m0 + (wave * NI + i) * (64 / SP::UK) + lane / SP::UK;
+            const int row = m / W;
+            px[i] = m - row * W;
+            py[i] = m < a.M ? row % H : INT32_MIN / 2;
+            at[i] = (uint32_t)m * (uint32_t)C * 4u + (u >> 1) * 16;
+        }
+    }
+
+    __device__ __forceinline__ void issue(int, char* stage)
+    {
+        const uint32_t off = (uint32_t)((dy * W + dx) * C + ci) * 4u;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const int iy = py[i] + dy, ix = px[i] + dx;
+            const bool in = taps > 0 && iy >= 0 && iy < H && ix >= 0 && ix < W;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                r, (__attribute__((address_space(3))) void*)(stage + (wave * NI + i) * 1024), 16,
+                (int)(in ? at[i] + off : OOB), 0, 0, 0);
+        }
+        ci += 16;
+#pragma unroll
+        for (int w = 0; w < 2; ++w) {  // 16 channels on are two taps at most
+            const bool wrap = ci >= C;
+            ci -= wrap ? C : 0;
+            dx += wrap;
+            taps -= wrap;
+            const bool line = dx > half;
+            dy += line;
+            dx = line ? -half : dx;
+        }
+    }
+};
+
+// Eight channels at a time: 32 bytes of X into 16 bytes of high and 16 of low
+// parts.
+__global__ void __launch_bounds__(256) conv_split_kernel(const float* X, char* out, int64_t groups)
+{
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < groups; i += (int64_t)gridDim.x * blockDim.x) {
+        const f32x4 v0 = *reinterpret_cast<const f32x4*>(X + 8 * i), v1 = *reinterpret_cast<const f32x4*>(X + 8 * i + 4);
+        const float x[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+        bf16x8 h, l;
+        split_bf16x8(x, h, l);
+        *reinterpret_cast<bf16x8*>(out + 32 * i) = h;
+        *reinterpret_cast<bf16x8*>(out + 32 * i + 16) = l;
+    }
+}
+
+template <class CF, int FR>
+__global__ void __launch_bounds__(CF::NT, CF::WAVES_PER_EU) conv_turns_kernel(PackedArgs a, ConvGeom g)
+{
+    static_assert(kPackK % CF::BK == 0 && kPackRows % CF::BN == 0, "panels and tiles divide the packing padding");
+    __shared__ __attribute__((aligned(1024))) char lds[CF::LDS_BYTES];
+    const TileCoord tc = map_tile(blockIdx.x, a.tiles_m, a.tiles_n, a.group_m, a.xcd_remap);
+    packed_tile<CF, ConvStepsA<CF, FR>>(a, tc.tm * CF::BM, tc.tn * CF::BN, lds, g);
+}
+
 template <class CF, int FR>
 __global__ void __launch_bounds__(CF::NT, CF::WAVES_PER_EU) conv_packed_kernel(PackedArgs a, ConvGeom g)
 {
@@ -199,6 +297,7 @@ namespace {
 struct ConvPacked {
     int dtype, mode, BM, BN, BK, NS, threads;
     void (*kernel[2])(PackedArgs, ConvGeom);  // [0]: 3 x 3, [1]: any R
+    bool turns = false;                       // TCfg: step-packed filter, X split unit by unit
 };
 
 #define TG_CONVP(DT, MODE, BM, BN, BK, WGM, WGN, NS)                         \
@@ -217,7 +316,9 @@ const ConvPacked kConvPacked[] = {
     TG_CONVP(TGEMM_F32, MODE_F32, 256, 256, 32, 2, 4, 2),
     TG_CONVP(TGEMM_F32, MODE_F32, 256, 128, 32, 2, 4, 3),
     TG_CONVP(TGEMM_F32_BF16X3, MODE_X3, 128, 128, 32, 2, 2, 2),
-    TG_CONVP(TGEMM_F32_BF16X3, MODE_X3, 256, 256, 32, 2, 4, 2),
+    {TGEMM_F32_BF16X3, MODE_X3, 256, 256, 32, 2, TCfg<MODE_X3, 256, 256, 2, 4, 4>::NT,
+     {&conv_turns_kernel<TCfg<MODE_X3, 256, 256, 2, 4, 4>, 3>, &conv_turns_kernel<TCfg<MODE_X3, 256, 256, 2, 4, 4>, 0>},
+     true},
     TG_CONVP(TGEMM_F32_BF16X3, MODE_X3, 256, 128, 32, 2, 4, 3),
     TG_CONVP(TGEMM_F32_BF16X3, MODE_X3, 128, 128, 16, 2, 2, 2),
 };
@@ -320,9 +421,17 @@ int conv_packed_run(const ConvPacked& p, int64_t M, int64_t Cin, int64_t Cout, i
     char* Blo = x3 ? Bp + Np * Kp * es : nullptr;
     char* Ah = x3 ? Bp + wbytes : nullptr;
     char* Al = x3 ? Ah + M * Cin * es : nullptr;
-    rc = launch_pack_cols(p.mode, Wt, Cout, K, Cout, Bp, Blo, Np, Kp, s);
-    if (rc == TGEMM_SUCCESS && x3) rc = launch_pack_rows(MODE_X3, X, Cin, M, Cin, Ah, Al, M, Cin, s);
-    if (rc != TGEMM_SUCCESS) return rc;
+    if (p.turns) {
+        rc = launch_step_cols(p.mode, Wt, Cout, K, Cout, Bp, Np, Kp, s);
+        if (rc != TGEMM_SUCCESS) return rc;
+        const int64_t groups = M * Cin / 8;
+        hipLaunchKernelGGL(conv_split_kernel, dim3((unsigned)std::min<int64_t>((groups + 255) / 256, 65536)), dim3(256),
+                           0, s, X, Ah, groups);
+    } else {
+        rc = launch_pack_cols(p.mode, Wt, Cout, K, Cout, Bp, Blo, Np, Kp, s);
+        if (rc == TGEMM_SUCCESS && x3) rc = launch_pack_rows(MODE_X3, X, Cin, M, Cin, Ah, Al, M, Cin, s);
+        if (rc != TGEMM_SUCCESS) return rc;
+    }
 
     PackedArgs a;
     std::memset(&a, 0, sizeof(a));

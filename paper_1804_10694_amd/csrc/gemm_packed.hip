@@ -58,6 +58,31 @@ __global__ void __launch_bounds__(256) pack_cols_kernel(const void* X, int64_t l
     pack_col_block<MODE>(X, ldx, K, N, P, Plo, Np, Kp, blockIdx.x * 64, blockIdx.y * 64, tile, vec != 0);
 }
 
+// Step order (StepPack): a block covers a part of one 256-row tile over two
+// consecutive steps, so that both halves of a 128-byte line of X are read at
+// once.
+template <int MODE>
+__global__ void __launch_bounds__(256) step_rows_kernel(const void* X, int64_t ldx, int R, int K, char* P, int Kp,
+                                                        int vec)
+{
+    using SP = StepPack<MODE>;
+    const uint32_t q = blockIdx.x % SP::GROUPS, rest = blockIdx.x / SP::GROUPS, pairs = Kp / (2 * SP::HK);
+    const uint32_t tile = rest / pairs, pair = rest - tile * pairs;
+    const int item = q * 256 + threadIdx.x;
+    const int r = tile * SP::ROWS + item / SP::GROUPS, g = item % SP::GROUPS;
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+        step_row_group<MODE>(X, ldx, R, K, P, Kp, r, (2 * pair + j) * SP::HK + g * SP::KU, vec != 0);
+}
+
+template <int MODE>
+__global__ void __launch_bounds__(256) step_cols_kernel(const void* X, int64_t ldx, int K, int N, char* P, int Kp,
+                                                        int vec)
+{
+    __shared__ float tile[64][66];
+    step_col_block<MODE>(X, ldx, K, N, P, Kp, blockIdx.x * 64, blockIdx.y * 64, tile, vec != 0);
+}
+
 template <class CF>
 __global__ void __launch_bounds__(CF::NT, CF::WAVES_PER_EU) packed_kernel(PackedArgs a)
 {
@@ -224,7 +249,9 @@ __global__ void __launch_bounds__(CF::NT, CF::WAVES_PER_EU) packed_sk_kernel(Pac
     const int v = (k.grid % kNumXcd == 0) ? ((int)blockIdx.x % kNumXcd) * per_xcd + (int)blockIdx.x / kNumXcd
                                           : (int)blockIdx.x;
     const int end = sk_begin(k, v + 1);
-    using AL = PackedRowsA<CF>;
+    using AL = typename TileParts<CF>::A;
+    using BL = typename TileParts<CF>::B;
+    using OP = typename TileParts<CF>::Op;
     for (int it = sk_begin(k, v); it < end;) {
         const int t = it / k.panels;
         const int pb = it - t * k.panels;
@@ -234,11 +261,9 @@ __global__ void __launch_bounds__(CF::NT, CF::WAVES_PER_EU) packed_sk_kernel(Pac
         const SkStore<CF> epi{TileStore<CF>{a, m0, n0}, SkPartial<CF>{a, k, t, v, m0, n0, &flag},
                               pb == 0 && pe == k.panels};
         if ((CF::MODE == MODE_BF16 || CF::MODE == MODE_FP8) && a.sA)
-            packed_tile_range<CF, AL, PackedRowsB<CF>, PackedOps<CF>, true>(a, m0, n0, lds, typename AL::Geom(),
-                                                                            pb, pe - pb, epi);
+            packed_tile_range<CF, AL, BL, OP, true>(a, m0, n0, lds, typename AL::Geom(), pb, pe - pb, epi);
         else
-            packed_tile_range<CF, AL, PackedRowsB<CF>, PackedOps<CF>, false>(a, m0, n0, lds, typename AL::Geom(),
-                                                                             pb, pe - pb, epi);
+            packed_tile_range<CF, AL, BL, OP, false>(a, m0, n0, lds, typename AL::Geom(), pb, pe - pb, epi);
         it += pe - pb;
         __syncthreads();  // every wave is done with the LDS stages (and the flag) before the next tile
     }
@@ -252,6 +277,7 @@ struct PSched {
     void (*kernel)(PackedArgs);
     void (*sk_kernel)(PackedArgs, SkArgs);  // stream-K form, or null
     int mfma;                               // MFMA block (32 or 16)
+    int step = 0;                           // k per step of step-packed operands (0: row-packed)
 };
 
 #define TG_PSCHED(DT, MODE, BM, BN, BK, WGM, WGN, NS)                                             \
@@ -268,6 +294,17 @@ struct PSched {
     {DT, MODE, BM, BN, BK, WGM, WGN, PCfg<MODE, BM, BN, BK, WGM, WGN, NS, 16>::LDS_BYTES,              \
      PCfg<MODE, BM, BN, BK, WGM, WGN, NS, 16>::NT, &packed_kernel<PCfg<MODE, BM, BN, BK, WGM, WGN, NS, 16>>, \
      nullptr, 16}
+
+// A schedule whose kernels take turns over steps of half its panel, in the same
+// LDS (TCfg): SK its stream-K form or null.
+template <int MODE, int BM, int BN, int WGM, int WGN, int MS, bool SK>
+constexpr PSched turns(int dtype, int BK)
+{
+    using CF = TCfg<MODE, BM, BN, WGM, WGN, 4, MS>;
+    void (*sk)(PackedArgs, SkArgs) = nullptr;
+    if constexpr (SK) sk = &packed_sk_kernel<CF>;
+    return {dtype, MODE, BM, BN, BK, WGM, WGN, CF::LDS_BYTES, CF::NT, &packed_kernel<CF>, sk, MS, CF::BK};
+}
 
 constexpr PSched kPacked[] = {
     // two workgroups per CU (LDS <= 80 KB), 4 waves each
@@ -288,14 +325,14 @@ constexpr PSched kPacked[] = {
     TG_PSCHED(TGEMM_F32, MODE_F32, 256, 256, 32, 2, 4, 2),
     TG_PSCHED(TGEMM_F32, MODE_F32, 256, 256, 16, 2, 4, 4),
     TG_PSCHED(TGEMM_F32, MODE_F32, 256, 128, 32, 2, 4, 3),
-    TG_PSCHED_SK(TGEMM_F32_BF16X3, MODE_X3, 256, 256, 32, 2, 4, 2),
+    turns<MODE_X3, 256, 256, 2, 4, 32, true>(TGEMM_F32_BF16X3, 32),
     TG_PSCHED(TGEMM_F32_BF16X3, MODE_X3, 256, 128, 32, 2, 4, 3),
     TG_PSCHED(TGEMM_F32_BF16X3, MODE_X3, 128, 128, 32, 2, 2, 2),
     TG_PSCHED_SK(TGEMM_BF16, MODE_BF16, 256, 256, 64, 2, 4, 2),
     TG_PSCHED(TGEMM_BF16, MODE_BF16, 256, 256, 32, 2, 4, 4),
     TG_PSCHED(TGEMM_BF16, MODE_BF16, 128, 128, 64, 2, 2, 2),
-    TG_PSCHED(TGEMM_FP8_E4M3, MODE_FP8, 256, 256, 128, 2, 4, 2),
-    TG_PSCHED_SK(TGEMM_FP8_E4M3, MODE_FP8, 256, 256, 128, 4, 2, 2),
+    turns<MODE_FP8, 256, 256, 2, 4, 32, false>(TGEMM_FP8_E4M3, 128),
+    turns<MODE_FP8, 256, 256, 4, 2, 32, true>(TGEMM_FP8_E4M3, 128),
     TG_PSCHED(TGEMM_FP8_E4M3, MODE_FP8, 256, 256, 64, 2, 4, 4),
     TG_PSCHED(TGEMM_FP8_E4M3, MODE_FP8, 128, 128, 128, 2, 2, 2),
     // 16 x 16 MFMA blocks (v_mfma_f32_16x16x4f32, 16x16x32_bf16, 16x16x128_f8f6f4)
@@ -542,6 +579,40 @@ int launch_pack_cols(int mode, const void* X, int64_t ldx, int64_t K, int64_t N,
     return hipGetLastError() == hipSuccess ? TGEMM_SUCCESS : TGEMM_LAUNCH_FAILED;
 }
 
+namespace {
+template <int MODE>
+int step_cols(const void* B, int64_t ldb, int64_t K, int64_t N, char* Bp, int64_t Np, int64_t Kp, hipStream_t s)
+{
+    static_assert(kPackRows == StepPack<MODE>::ROWS && kPackK % (2 * StepPack<MODE>::HK) == 0,
+                  "packing padding holds whole chunks and pairs of steps");
+    if (Kp / 64 > 65535) return TGEMM_NOT_SUPPORTED;
+    hipLaunchKernelGGL(step_cols_kernel<MODE>, dim3((unsigned)(Np / 64), (unsigned)(Kp / 64)), dim3(256), 0, s, B, ldb,
+                       (int)K, (int)N, Bp, (int)Kp, pack_cols_vec(B, ldb, src_bytes<MODE>()));
+    return hipGetLastError() == hipSuccess ? TGEMM_SUCCESS : TGEMM_LAUNCH_FAILED;
+}
+
+template <int MODE>
+int launch_step_pack(const void* A, int64_t lda, int64_t M, char* Ap, int64_t Mp, const void* B, int64_t ldb,
+                     int64_t N, char* Bp, int64_t Np, int64_t K, int64_t Kp, hipStream_t s)
+{
+    using SP = StepPack<MODE>;
+    constexpr int es = src_bytes<MODE>();
+    const int64_t blocks = Mp / SP::ROWS * (Kp / (2 * SP::HK)) * SP::GROUPS;
+    if (blocks > INT32_MAX) return TGEMM_NOT_SUPPORTED;
+    const uintptr_t pa = reinterpret_cast<uintptr_t>(A);
+    const int vec_a = es == 4 || (pa % 16 == 0 && lda * es % 16 == 0);
+    hipLaunchKernelGGL(step_rows_kernel<MODE>, dim3((unsigned)blocks), dim3(256), 0, s, A, lda, (int)M, (int)K, Ap,
+                       (int)Kp, vec_a);
+    return step_cols<MODE>(B, ldb, K, N, Bp, Np, Kp, s);
+}
+}  // namespace
+
+int launch_step_cols(int mode, const void* X, int64_t ldx, int64_t K, int64_t N, char* P, int64_t Np, int64_t Kp,
+                     hipStream_t s)
+{
+    return mode == MODE_X3 ? step_cols<MODE_X3>(X, ldx, K, N, P, Np, Kp, s) : TGEMM_INTERNAL;
+}
+
 // Pack A and B into `ws` and run packed schedule `pid` (index into kPacked).
 bool packed_k_ok(int64_t K, int dtype)
 {
@@ -562,15 +633,22 @@ int run_packed_ws(int pid, int64_t M, int64_t N, int64_t K, float alpha, const v
     const int64_t Mp = (M + kPackRows - 1) / kPackRows * kPackRows;
     const int64_t Np = (N + kPackRows - 1) / kPackRows * kPackRows;
     const int64_t es = p.dtype == TGEMM_FP8_E4M3 ? 1 : p.dtype == TGEMM_F32 ? 4 : 2;
-    const int64_t Kp = packed_kp(K, es);
+    const int64_t Kp = p.step ? (K + kPackK - 1) / kPackK * kPackK : packed_kp(K, es);
     char* base = static_cast<char*>(ws);
     char* Ap = base;
     char* Alo = p.mode == MODE_X3 ? Ap + Mp * Kp * es : nullptr;
     char* Bp = base + Mp * Kp * es * (p.mode == MODE_X3 ? 2 : 1);
     char* Blo = p.mode == MODE_X3 ? Bp + Np * Kp * es : nullptr;
 
-    int rc = launch_pack_rows(p.mode, A, lda, M, K, Ap, Alo, Mp, Kp, s);
-    if (rc == TGEMM_SUCCESS) rc = launch_pack_cols(p.mode, B, ldb, K, N, Bp, Blo, Np, Kp, s);
+    int rc;
+    if (p.step) {
+        rc = p.mode == MODE_FP8    ? launch_step_pack<MODE_FP8>(A, lda, M, Ap, Mp, B, ldb, N, Bp, Np, K, Kp, s)
+             : p.mode == MODE_BF16 ? launch_step_pack<MODE_BF16>(A, lda, M, Ap, Mp, B, ldb, N, Bp, Np, K, Kp, s)
+                                   : launch_step_pack<MODE_X3>(A, lda, M, Ap, Mp, B, ldb, N, Bp, Np, K, Kp, s);
+    } else {
+        rc = launch_pack_rows(p.mode, A, lda, M, K, Ap, Alo, Mp, Kp, s);
+        if (rc == TGEMM_SUCCESS) rc = launch_pack_cols(p.mode, B, ldb, K, N, Bp, Blo, Np, Kp, s);
+    }
     if (rc != TGEMM_SUCCESS) return rc;
     PackedArgs a;
     a.A = Ap;
@@ -597,7 +675,8 @@ int run_packed_ws(int pid, int64_t M, int64_t N, int64_t K, float alpha, const v
     const int tiles = a.tiles_m * a.tiles_n;
     if (sk) {
         SkArgs k;
-        k.panels = (int)((K + p.BK - 1) / p.BK);
+        const int bk = p.step ? p.step : p.BK;
+        k.panels = (int)((K + bk - 1) / bk);
         const int64_t total = (int64_t)tiles * k.panels;
         if (tiles > kSkMaxTiles || total > INT32_MAX || !cnt) return TGEMM_NOT_SUPPORTED;
         k.total = (int)total;

@@ -60,6 +60,9 @@ int launch_pack_rows(int mode, const void* X, int64_t ldx, int64_t R, int64_t K,
                      int64_t Rp, int64_t Kp, hipStream_t s);
 int launch_pack_cols(int mode, const void* X, int64_t ldx, int64_t K, int64_t N, void* P, void* Plo,
                      int64_t Np, int64_t Kp, hipStream_t s);
+// pack cols into step order (StepPack, tile_packed.h; x3), Kp a multiple of kPackK.
+int launch_step_cols(int mode, const void* X, int64_t ldx, int64_t K, int64_t N, char* P, int64_t Np, int64_t Kp,
+                     hipStream_t s);
 constexpr int kPackRows = 256;  // packed row counts of the gemm path are multiples of this
 constexpr int kPackK = 128;     // packed K of the gemm path is a multiple of this (elements)
 // Packed row length (elements) of the gemm path for K and an element size of

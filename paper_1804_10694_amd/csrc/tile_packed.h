@@ -131,6 +131,49 @@ __device__ __forceinline__ void pack_row_group(const void* X, int64_t ldx, int R
 // can be reused at once.  Four elements inside the matrix take one vector
 // load: floats always (16 bytes at any 4-byte alignment), codes when vec says
 // the rows of X are aligned for it.
+template <int ES, class PUT>
+__device__ __forceinline__ void read_col_block(const void* X, int64_t ldx, int K, int N, int n0, int k0, bool vec,
+                                               const PUT& put)
+{
+    const int t = threadIdx.x;
+    const int n4 = t & 15, kr = t >> 4;  // 16 x 16 threads; 4 passes over 64 rows
+    const int n = n0 + 4 * n4;
+#pragma unroll
+    for (int pass = 0; pass < 4; ++pass) {
+        const int kk = kr + 16 * pass, k = k0 + kk;
+        const char* src = static_cast<const char*>(X) + ((int64_t)k * ldx + n) * ES;
+        float v[4];
+        if ((ES == 4 || vec) && k < K && n + 4 <= N) {
+            if (ES == 4) {
+                const f32x4 x = *reinterpret_cast<const f32x4u*>(src);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) v[c] = x[c];
+            } else if (ES == 2) {
+                const uint2 x = *reinterpret_cast<const uint2*>(src);
+                v[0] = __uint_as_float(x.x & 0xffffu);
+                v[1] = __uint_as_float(x.x >> 16);
+                v[2] = __uint_as_float(x.y & 0xffffu);
+                v[3] = __uint_as_float(x.y >> 16);
+            } else {
+                const uint32_t x = *reinterpret_cast<const uint32_t*>(src);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) v[c] = __uint_as_float((x >> (8 * c)) & 0xffu);
+            }
+        } else {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                v[c] = 0.f;
+                if (k < K && n + c < N) {
+                    if (ES == 4) v[c] = reinterpret_cast<const float*>(src)[c];
+                    else if (ES == 2) v[c] = __uint_as_float(reinterpret_cast<const uint16_t*>(src)[c]);
+                    else v[c] = __uint_as_float(reinterpret_cast<const uint8_t*>(src)[c]);
+                }
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) put(kk, 4 * n4 + c, v[c]);
+    }
+}
 template <int MODE>
 __device__ __forceinline__ void pack_col_block(const void* X, int64_t ldx, int K, int N, void* P,
                                                void* Plo, int Np, int Kp, int n0, int k0,
@@ -138,45 +181,7 @@ __device__ __forceinline__ void pack_col_block(const void* X, int64_t ldx, int K
 {
     constexpr int ES = src_bytes<MODE>();
     const int t = threadIdx.x;
-    {
-        const int n4 = t & 15, kr = t >> 4;  // 16 x 16 threads; 4 passes over 64 rows
-        const int n = n0 + 4 * n4;
-#pragma unroll
-        for (int pass = 0; pass < 4; ++pass) {
-            const int kk = kr + 16 * pass, k = k0 + kk;
-            const char* src = static_cast<const char*>(X) + ((int64_t)k * ldx + n) * ES;
-            float v[4];
-            if ((ES == 4 || vec) && k < K && n + 4 <= N) {
-                if (ES == 4) {
-                    const f32x4 x = *reinterpret_cast<const f32x4u*>(src);
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) v[c] = x[c];
-                } else if (ES == 2) {
-                    const uint2 x = *reinterpret_cast<const uint2*>(src);
-                    v[0] = __uint_as_float(x.x & 0xffffu);
-                    v[1] = __uint_as_float(x.x >> 16);
-                    v[2] = __uint_as_float(x.y & 0xffffu);
-                    v[3] = __uint_as_float(x.y >> 16);
-                } else {
-                    const uint32_t x = *reinterpret_cast<const uint32_t*>(src);
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) v[c] = __uint_as_float((x >> (8 * c)) & 0xffu);
-                }
-            } else {
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    v[c] = 0.f;
-                    if (k < K && n + c < N) {
-                        if (ES == 4) v[c] = reinterpret_cast<const float*>(src)[c];
-                        else if (ES == 2) v[c] = __uint_as_float(reinterpret_cast<const uint16_t*>(src)[c]);
-                        else v[c] = __uint_as_float(reinterpret_cast<const uint8_t*>(src)[c]);
-                    }
-                }
-            }
-#pragma unroll
-            for (int c = 0; c < 4; ++c) tile[kk][4 * n4 + c] = v[c];
-        }
-    }
+    read_col_block<ES>(X, ldx, K, N, n0, k0, vec, [&](int kk, int nn, float v) { tile[kk][nn] = v; });
     __syncthreads();
     {
         const int nn = t >> 2, kq = t & 3;  // packed row n0 + nn, k0 + 16 kq .. + 15
@@ -229,6 +234,7 @@ struct PCfg {
     static constexpr int MODE = MODE_, BM = BM_, BN = BN_, BK = BK_, WGM = WGM_, WGN = WGN_;
     static constexpr int NS = NS_;  // LDS stages (panels in flight = NS - 1)
     static constexpr int MS = MS_;
+    static constexpr bool TURNS = false;                 // see TCfg
     static constexpr int LG = 64 / MS;                   // lane groups along k of one MFMA
     static constexpr int AR = MS * MS / 64;              // accumulator registers per lane per block
     using Acc = typename std::conditional<MS == 32, f32x16, f32x4>::type;
@@ -269,6 +275,33 @@ struct PCfg {
     static_assert(WTM % MS == 0 && WTN % MS == 0, "whole blocks");
     static_assert(MS == 32 || MS == 16, "MFMA block");
     static_assert(LDS_BYTES <= 160 * 1024, "LDS");
+};
+
+// Tiles whose main loop alternates between two groups of waves (see
+// packed_tile_range): eight waves, panels of one MFMA cluster per wave
+// ("steps": four 16-byte units per row), NS of them in a ring, operands packed
+// in step order (StepPack).
+template <int MODE_, int BM_, int BN_, int WGM_, int WGN_, int NS_, int MS_ = 32>
+struct TCfg : PCfg<MODE_, BM_, BN_, MODE_ == MODE_FP8 ? 64 : MODE_ == MODE_BF16 ? 32 : 16, WGM_, WGN_, NS_, MS_> {
+    static constexpr bool TURNS = true;
+    static_assert(WGM_ * WGN_ == 8 && MODE_ != MODE_F32, "two waves per SIMD, bf16 or e4m3 matrix cores");
+};
+
+// Step-packed operands.  A step holds four units of a row: 32 k (bf16), 64 k
+// (e4m3), or 16 k as two units of high and two of low parts (x3).  256 rows by
+// one step form a chunk of 16 KB in the very order LDS holds it (pk_slot), and
+// the chunks of a tile follow each other along k, so a workgroup streams its
+// operand front to back and every load instruction moves one run of 1 KB.
+// (Rows of 64 bytes per panel, as row-packed operands would have here, load at
+// half the rate: on MI355X from L2 73 against 130 bytes per ns and CU.)
+template <int MODE>
+struct StepPack {
+    static constexpr int KU = (MODE == MODE_FP8) ? 16 : 8;            // k per unit
+    static constexpr int UK = 4;                                      // units per row and step
+    static constexpr int HK = (MODE == MODE_X3 ? 2 : 4) * KU;         // k per step
+    static constexpr int GROUPS = HK / KU;                            // groups of KU k per row and step
+    static constexpr int ROWS = 256;
+    static constexpr int CHUNK = ROWS * UK * 16;                      // bytes
 };
 
 // Physical unit of (row, logical unit u): rows of UK units, u XORed with bits
@@ -548,6 +581,18 @@ __device__ __forceinline__ float block_scale(const PackedArgs& a, int row0, int 
     block_scales(a, row0, col0, kb, sa, sb);
     return sa * sb;
 }
+// The same as scalar loads with no branch (a block of padding takes the last
+// tile's scales): the loop that takes turns counts its panel loads in vmcnt,
+// and waits for lgkmcnt(0) every step anyway.
+__device__ __forceinline__ void block_scales_scalar(const PackedArgs& a, int row0, int col0, int kb, float& sa,
+                                                    float& sb)
+{
+    using Scalar = const __attribute__((address_space(4))) float*;
+    const int ra = __builtin_amdgcn_readfirstlane(min(row0, a.M - 1) / 128);
+    const int cb = __builtin_amdgcn_readfirstlane(min(col0, a.N - 1) / 128);
+    sa = ((Scalar)a.sA)[ra * a.lds_a + kb];
+    sb = ((Scalar)a.sB)[kb * a.lds_b + cb];
+}
 
 // A float32 scale s as 2^(e8 - 127) * m with e8 its biased exponent (the E8M0
 // byte the e4m3 matrix core applies exactly) and m in [1, 2) (sign kept);
@@ -618,6 +663,176 @@ struct PackedRowsB {
             load_panel<CF::UK, CF::B_INSTR>(rl, lane_off, row_bytes, kb, stage + CF::LDS_B, wave);
     }
 };
+
+// Panel loads of step-packed operands.
+template <class CF, int ROWS_T>
+struct StepRows {
+    using SP = StepPack<CF::MODE>;
+    static constexpr int NI = ROWS_T * SP::UK / 64 / CF::NW;  // loads per wave and step
+    static constexpr int LOADS = NI;
+    const char* base;
+    int off, wave;
+
+    __device__ __forceinline__ void start(const char* rows, int r0, int Kp, int lane, int wave_)
+    {
+        static_assert(CF::BK == SP::HK && SP::ROWS % ROWS_T == 0 && NI >= 1, "steps");
+        wave = wave_;
+        base = rows + (int64_t)(r0 / SP::ROWS) * (Kp / SP::HK) * SP::CHUNK + (r0 % SP::ROWS) * (SP::UK * 16);
+        off = lane * 16;
+    }
+
+    __device__ __forceinline__ void load(int step, char* dst) const
+    {
+        const __amdgpu_buffer_rsrc_t r = make_rsrc(base + (int64_t)step * SP::CHUNK, ROWS_T * SP::UK * 16);
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const int ig = wave * NI + i;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                r, (__attribute__((address_space(3))) void*)(dst + ig * 1024), 16, off, ig * 1024, 0, 0);
+        }
+    }
+};
+template <class CF>
+struct StepRowsA : StepRows<CF, CF::BM> {
+    struct Geom {};
+    __device__ __forceinline__ void init(const PackedArgs& a, int m0, int lane, int wave, const Geom&)
+    {
+        this->start(a.A, m0, a.Kp, lane, wave);
+    }
+    __device__ __forceinline__ void issue(int step, char* stage) const { this->load(step, stage); }
+};
+template <class CF>
+struct StepRowsB : StepRows<CF, CF::BN> {
+    __device__ __forceinline__ void init(const PackedArgs& a, int n0, int lane, int wave)
+    {
+        this->start(a.B, n0, a.Kp, lane, wave);
+    }
+    __device__ __forceinline__ void issue(int step, char* stage) const { this->load(step, stage); }
+};
+
+// Operand policy over a step's LDS layout: group g of a lane's MFMA k group,
+// array x (hi, lo) is unit (LG g + lane group) * UPL + v (x3: 2 x + lane half).
+template <class CF>
+struct StepOps : PackedOps<CF> {
+    using typename PackedOps<CF>::Ops;
+    __device__ __forceinline__ static void load(const char* stage, Ops& o, int g, int wm0, int wn0, int lane)
+    {
+        constexpr int UK = StepPack<CF::MODE>::UK, MS = CF::MS;
+        const int h = lane / MS, l32 = lane & (MS - 1);
+        const char* lb = stage + CF::NARR * CF::LDS_A;
+#pragma unroll
+        for (int v = 0; v < PkOps<CF>::AV; ++v)
+#pragma unroll
+            for (int x = 0; x < PkOps<CF>::NA; ++x) {
+                const int u = CF::MODE == MODE_X3 ? 2 * x + h : (CF::LG * g + h) * CF::UPL + v;
+#pragma unroll
+                for (int i = 0; i < CF::TM; ++i)
+                    o.a[x][i][v] = *reinterpret_cast<const u32x4*>(stage + pk_slot<UK>(wm0 + MS * i + l32, u) * 16);
+#pragma unroll
+                for (int j = 0; j < CF::TN; ++j)
+                    o.b[x][j][v] = *reinterpret_cast<const u32x4*>(lb + pk_slot<UK>(wn0 + MS * j + l32, u) * 16);
+            }
+    }
+};
+
+// The loaders and operand policy of a configuration.
+template <class CF, bool T = CF::TURNS>
+struct TileParts {
+    using A = PackedRowsA<CF>;
+    using B = PackedRowsB<CF>;
+    using Op = PackedOps<CF>;
+};
+template <class CF>
+struct TileParts<CF, true> {
+    using A = StepRowsA<CF>;
+    using B = StepRowsB<CF>;
+    using Op = StepOps<CF>;
+};
+
+// A-side packing into steps, KU consecutive k (k0 ..) of row r: bytes copied
+// for codes, split into a high and a low unit for x3; zero beyond R and K.
+// Vector loads as in pack_row_group (e4m3: 16 codes, when vec says so).
+template <int MODE>
+__device__ __forceinline__ void step_row_group(const void* X, int64_t ldx, int R, int K, char* P, int Kp, int r, int k0,
+                                               bool vec)
+{
+    using SP = StepPack<MODE>;
+    constexpr int ES = src_bytes<MODE>();
+    const bool whole = (ES == 4 || vec) && r < R && k0 + SP::KU <= K;
+    const char* src = static_cast<const char*>(X) + ((int64_t)r * ldx + k0) * ES;
+    const int row = r % SP::ROWS, g = k0 % SP::HK / SP::KU;
+    char* dst = P + ((int64_t)(r / SP::ROWS) * (Kp / SP::HK) + k0 / SP::HK) * SP::CHUNK;
+    if constexpr (MODE == MODE_X3) {
+        float x[8];
+        if (whole) {
+            const f32x4 v0 = *reinterpret_cast<const f32x4u*>(src), v1 = *reinterpret_cast<const f32x4u*>(src + 16);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                x[e] = v0[e];
+                x[4 + e] = v1[e];
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) x[e] = (r < R && k0 + e < K) ? reinterpret_cast<const float*>(src)[e] : 0.f;
+        }
+        bf16x8 h, l;
+        split_bf16x8(x, h, l);
+        *reinterpret_cast<bf16x8*>(dst + pk_slot<SP::UK>(row, g) * 16) = h;
+        *reinterpret_cast<bf16x8*>(dst + pk_slot<SP::UK>(row, 2 + g) * 16) = l;
+    } else {
+        u32x4 w = {0, 0, 0, 0};
+        if (whole) {
+            w = *reinterpret_cast<const u32x4*>(src);
+        } else if (r < R) {
+#pragma unroll
+            for (int e = 0; e < SP::KU; ++e)
+                if (k0 + e < K) {
+                    const uint32_t c = ES == 2 ? reinterpret_cast<const uint16_t*>(src)[e]
+                                               : reinterpret_cast<const uint8_t*>(src)[e];
+                    w[e * ES / 4] |= c << (8 * (e * ES % 4));
+                }
+        }
+        *reinterpret_cast<u32x4*>(dst + pk_slot<SP::UK>(row, g) * 16) = w;
+    }
+}
+
+// B-side packing into steps, one 64 x 64 block (n0, k0) of X (K x N) through
+// the LDS tile (rows of 66 floats: the eight k a lane collects for its unit
+// fall on banks 16 apart for the four units of a row).  Zero beyond K and N.
+// 256 threads.
+template <int MODE>
+__device__ __forceinline__ void step_col_block(const void* X, int64_t ldx, int K, int N, char* P, int Kp, int n0,
+                                               int k0, float (&tile)[64][66], bool vec)
+{
+    using SP = StepPack<MODE>;
+    constexpr int ES = src_bytes<MODE>();
+    const int t = threadIdx.x;
+    read_col_block<ES>(X, ldx, K, N, n0, k0, vec, [&](int kk, int nn, float v) { tile[kk][nn] = v; });
+    __syncthreads();
+    constexpr int PER = 64 / SP::KU;  // groups of KU k per column of the block
+#pragma unroll
+    for (int i = 0; i < 64 * PER / 256; ++i) {
+        const int id = i * 256 + t;
+        const int g = id % SP::GROUPS, nn = id / SP::GROUPS % 64, st = id / (SP::GROUPS * 64);
+        const int n = n0 + nn, row = n % SP::ROWS, kk = (st * SP::GROUPS + g) * SP::KU;
+        char* dst = P + ((int64_t)(n / SP::ROWS) * (Kp / SP::HK) + (k0 + kk) / SP::HK) * SP::CHUNK;
+        if constexpr (MODE == MODE_X3) {
+            float x[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) x[e] = tile[kk + e][nn];
+            bf16x8 h, l;
+            split_bf16x8(x, h, l);
+            *reinterpret_cast<bf16x8*>(dst + pk_slot<SP::UK>(row, g) * 16) = h;
+            *reinterpret_cast<bf16x8*>(dst + pk_slot<SP::UK>(row, 2 + g) * 16) = l;
+        } else {
+            u32x4 w = {0, 0, 0, 0};
+#pragma unroll
+            for (int e = 0; e < SP::KU; ++e)
+                w[e * ES / 4] |= __float_as_uint(tile[kk + e][nn]) << (8 * (e * ES % 4));
+            *reinterpret_cast<u32x4*>(dst + pk_slot<SP::UK>(row, g) * 16) = w;
+        }
+    }
+}
 
 // Epilogue of a whole tile: C = alpha * scale * acc (+ beta * C), predicated
 // only on partial tiles.  sc(i, j) is the scale product that multiplies the
@@ -704,13 +919,17 @@ __device__ __forceinline__ void packed_tile_range(const PackedArgs& a, int m0, i
     // the product of their mantissas, m = fl32(ma * mb) = fl32(sA * sB) / 2^E;
     // with power-of-two scales m stays 1 and acc is never rescaled.
     constexpr bool mx = scaled && one_scale && CF::MODE == MODE_FP8;
+    // raw: sa_next and sc_next hold the next block's two scales as loaded
+    constexpr bool raw = mx || (scaled && CF::TURNS);
+    static_assert(!CF::TURNS || one_scale, "one scale product per wave");
     int kb_cur = (p0 * CF::BK) / 128;
     float sc_cur[SM][SN], sc_next[SM][SN];  // mx: sc_cur holds m, sc_next the raw sB
     int e8a = 127, e8b = 127;
     float sa_next = 1.f;
     auto load_scales = [&](int kb, float (&dst)[SM][SN]) {
-        if constexpr (mx) {
-            block_scales(a, m0 + wm0, n0 + wn0, kb, sa_next, dst[0][0]);
+        if constexpr (raw) {
+            if constexpr (CF::TURNS) block_scales_scalar(a, m0 + wm0, n0 + wn0, kb, sa_next, dst[0][0]);
+            else block_scales(a, m0 + wm0, n0 + wn0, kb, sa_next, dst[0][0]);
         } else {
 #pragma unroll
             for (int i = 0; i < SM; ++i)
@@ -719,8 +938,10 @@ __device__ __forceinline__ void packed_tile_range(const PackedArgs& a, int m0, i
                     dst[i][j] = block_scale(a, m0 + wm0 + CF::MS * i, n0 + wn0 + CF::MS * j, kb);
         }
     };
-    // the unit of the block whose raw scales are sa_next and sc_next (mx)
-    auto mx_unit = [&](int& ea, int& eb) {
+    // the unit of the block whose raw scales are sa_next and sc_next: their product
+    // (mx: of the mantissas; the powers of two go to ea and eb)
+    auto unit = [&](int& ea, int& eb) {
+        if constexpr (!mx) return sa_next * sc_next[0][0];
         float ma, mb;
         split_scale(sa_next, ea, ma);
         split_scale(sc_next[0][0], eb, mb);
@@ -728,7 +949,7 @@ __device__ __forceinline__ void packed_tile_range(const PackedArgs& a, int m0, i
     };
     // issued before the first panels, so the first panel's wait covers them
     if constexpr (scaled) {
-        if constexpr (mx) {
+        if constexpr (raw) {
             load_scales(kb_cur, sc_next);
         } else {
             load_scales(kb_cur, sc_cur);
@@ -739,24 +960,46 @@ __device__ __forceinline__ void packed_tile_range(const PackedArgs& a, int m0, i
     constexpr int NS = CF::NS, L = AL::LOADS + BL::LOADS;
     static_assert((NS - 2) * L <= 63, "vmcnt holds at most 63");
     for (int p = 0; p < NS - 1 && p < npanel; ++p) issue(p, lds + p * CF::LDS_STAGE);
-    bool first_block = true;  // mx: the unit of the first block is set at its first panel
+    bool unit_one = false;    // raw: the current unit is 1
+    bool first_block = true;  // raw: the unit of the first block is set at its first panel
     auto prefetch = [&](int s) {  // during panel s: the scales of panel s + 1 if it opens a block
-        if (!scaled || s + 1 >= npanel) return;
-        const int kb = ((p0 + s + 1) * CF::BK) / 128;
-        if (kb != ((p0 + s) * CF::BK) / 128) load_scales(kb, sc_next);
+        if (!scaled || (s + 1 >= npanel && !CF::TURNS)) return;
+        const int kb = ((p0 + min(s + 1, npanel - 1)) * CF::BK) / 128;
+        if constexpr (CF::TURNS) load_scales(kb, sc_next);  // every step: no branch to wait behind
+        else if (kb != ((p0 + s) * CF::BK) / 128) load_scales(kb, sc_next);
     };
     // new K scale block at panel s: move acc to the new block's scale product
     auto rescale = [&](int s) {
         if (!scaled) return;
         const int kb = ((p0 + s) * CF::BK) / 128;
-        if constexpr (mx) {
+        if constexpr (raw) {
             if (first_block) {
                 first_block = false;
-                sc_cur[0][0] = mx_unit(e8a, e8b);
+                sc_cur[0][0] = unit(e8a, e8b);
+                unit_one = __builtin_amdgcn_readfirstlane(__float_as_uint(sc_cur[0][0])) == 0x3f800000u;
                 return;
             }
             if (kb == kb_cur) return;
-            const float m = mx_unit(e8a, e8b);
+            kb_cur = kb;
+            if constexpr (mx && CF::TURNS) {
+                // two powers of two after two powers of two: only the exponents move
+                const uint32_t ua = __float_as_uint(sa_next), ub = __float_as_uint(sc_next[0][0]);
+                const uint32_t ea = ua >> 23, eb = ub >> 23;
+                if (unit_one && ((ua | ub) & 0x007fffffu) == 0 && ea - 1u < 254u && eb - 1u < 254u) {
+                    e8a = (int)ea;
+                    e8b = (int)eb;
+                    return;
+                }
+            }
+            const float m = unit(e8a, e8b);
+            if constexpr (CF::TURNS) {
+                const uint32_t um = __builtin_amdgcn_readfirstlane(__float_as_uint(m));
+                unit_one = um == 0x3f800000u;
+                // the same finite, non-zero unit again: nothing to divide
+                if (um == __builtin_amdgcn_readfirstlane(__float_as_uint(sc_cur[0][0])) &&
+                    (um & 0x7fffffffu) - 1u < 0x7f7fffffu)
+                    return;
+            }
             const float ratio = sc_cur[0][0] / m;
             if (ratio != 1.f) {
 #pragma unroll
@@ -767,7 +1010,6 @@ __device__ __forceinline__ void packed_tile_range(const PackedArgs& a, int m0, i
                         for (int r = 0; r < CF::AR; ++r) acc[i][j][r] *= ratio;
             }
             sc_cur[0][0] = m;
-            kb_cur = kb;
             return;
         }
         if (s == 0 || kb == kb_cur) return;
@@ -798,7 +1040,65 @@ __device__ __forceinline__ void packed_tile_range(const PackedArgs& a, int m0, i
             for (int j = 0; j < SN; ++j) sc_cur[i][j] = sc_next[i][j];
         kb_cur = kb;
     };
-    if constexpr (NS == 2 && (CF::MODE == MODE_FP8 || (CF::NG == 1 && CF::BM >= 128))) {
+    if constexpr (CF::TURNS) {
+        // Two groups of four waves, one wave of each on every SIMD, take turns:
+        // in each slot one group reads a step's operands from LDS (and issues
+        // its share of the loads of step s + NS - 1) while the other runs the
+        // MFMAs of a step from registers, and a barrier ends the slot.  Group 1
+        // runs one slot late:
+        //     slot     2s      2s + 1
+        //     group 0  read s  mfma s
+        //     group 1  mfma s-1  read s
+        // Ring stage (s - 1) % NS was last read in slot 2s - 1, so both groups may
+        // refill it from their read of step s on.  Step s + 1 is first read in
+        // slot 2s + 2: each wave waits for its loads of it at the end of its own
+        // read of step s (slot 2s or 2s + 1), when those of the NS - 2 later steps
+        // may still fly.  (Waiting there in both groups leaves the MFMA slot
+        // without a branch, past which the compiler would move the MFMAs.)
+        //
+        // Why: with two stages of a whole panel the loads of a panel had one
+        // panel (2048 MFMA cycles) to land, less than the Infinity Cache takes,
+        // and all eight waves met at each panel's start to wait for the same
+        // LDS reads.  The barriers cost nothing here: without loads and reads
+        // the loop runs at the matrix cores' rate (bf16 1920 TFLOP/s).
+        const bool second = wave >= CF::NW / 2;
+        typename OP::Ops ops[CF::NG];
+        auto slot_end = [&] {
+            __builtin_amdgcn_sched_barrier(0);
+            lds_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto landed = [&](int s) {  // this wave's loads of step s + 1
+            if (s + NS - 1 < npanel) wait_vmcnt<(NS - 2) * L>();
+            else wait_vmcnt<0>();
+        };
+        if constexpr (scaled) rescale(0);
+        landed(-1);
+        slot_end();
+        if (second) slot_end();
+        for (int s = 0; s < npanel; ++s) {
+            const char* stage = lds + (s % NS) * CF::LDS_STAGE;
+            rescale(s);   // consumes the scales loaded during step s - 1 ...
+            prefetch(s);  // ... before they are replaced by those of step s + 1
+#pragma unroll
+            for (int g = 0; g < CF::NG; ++g) OP::load(stage, ops[g], g, wm0, wn0, lane);
+            if (s + NS - 1 < npanel) issue(s + NS - 1, lds + ((s + NS - 1) % NS) * CF::LDS_STAGE);
+            wait_lds_reads();
+            landed(s);
+            slot_end();
+            __builtin_amdgcn_s_setprio(1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int g = 0; g < CF::NG; ++g) {
+                if constexpr (mx) OP::compute(ops[g], acc, e8a, e8b);
+                else OP::compute(ops[g], acc);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_setprio(0);
+            slot_end();
+        }
+        if (!second) slot_end();
+    } else if constexpr (NS == 2 && (CF::MODE == MODE_FP8 || (CF::NG == 1 && CF::BM >= 128))) {
         // Two stages, refilled early: panel s + 2 goes into panel s's stage as
         // soon as every wave holds the operands of its last group of panel s (a
         // barrier before that group's MFMAs), so its loads have the rest of panel
@@ -899,7 +1199,8 @@ __device__ __forceinline__ void packed_tile_range(const PackedArgs& a, int m0, i
 }
 
 // One whole macro-tile (all K panels) with the standard epilogue.
-template <class CF, class AL = PackedRowsA<CF>, class BL = PackedRowsB<CF>, class OP = PackedOps<CF>>
+template <class CF, class AL = typename TileParts<CF>::A, class BL = typename TileParts<CF>::B,
+          class OP = typename TileParts<CF>::Op>
 __device__ __forceinline__ void packed_tile(const PackedArgs& a, int m0, int n0, char* lds,
                                             const typename AL::Geom& geom = typename AL::Geom())
 {
