@@ -156,6 +156,14 @@ int run_gemm(int id, int64_t M, int64_t N, int64_t K, float alpha, const void* A
     return launch_gemm(d, a, stream) == hipSuccess ? TGEMM_SUCCESS : TGEMM_LAUNCH_FAILED;
 }
 
+// A packing workspace that could not be had, for a bf16 or e4m3 problem that
+// direct tiles serve well enough.
+static bool no_room(int rc, int dtype, int64_t M, int64_t N, int64_t K)
+{
+    return rc == TGEMM_ALLOC_FAILED && (dtype == TGEMM_BF16 || dtype == TGEMM_FP8_E4M3) &&
+           !scaled_needs_packing(M, N, K);
+}
+
 // A float32 problem as the selection chose: on a register tile where the rule
 // names one that serves the operands, else on the schedule.
 int run_choice(const Choice& ch, int64_t M, int64_t N, int64_t K, float alpha, const void* A, int64_t lda,
@@ -216,7 +224,9 @@ int tgemm(int64_t M, int64_t N, int64_t K, float alpha, const void* A, int64_t l
         // a packed schedule whose workspace would have to grow under capture, or an
         // in-place one whose rows lie past the reach of its buffer offsets: use the
         // rule's schedule without packing instead
-        if (rc != TGEMM_CAPTURE_UNPLANNED && !(rc == TGEMM_NOT_SUPPORTED && schedule(ch.id).inplace)) return rc;
+        if (rc != TGEMM_CAPTURE_UNPLANNED && !(rc == TGEMM_NOT_SUPPORTED && schedule(ch.id).inplace) &&
+            !no_room(rc, dtype, M, N, K))
+            return rc;
         if ((rc = direct_schedule(M, N, K, dtype, vok, &ch)) != TGEMM_SUCCESS) return rc;
     }
     return rc;
@@ -266,7 +276,7 @@ int tgemm_scaled(int64_t M, int64_t N, int64_t K, float alpha, const void* A, in
     if (rc != TGEMM_SUCCESS) return rc;
     rc = run_scaled(M, N, K, alpha, A, lda, scaleA, B, ldb, scaleB, beta, C, ldc, dtype, ch.id,
                     ch.group_m, ch.xcd_remap, s);
-    if (rc != TGEMM_CAPTURE_UNPLANNED) return rc;
+    if (rc != TGEMM_CAPTURE_UNPLANNED && !no_room(rc, dtype, M, N, K)) return rc;
     if ((rc = direct_schedule(M, N, K, dtype, vok, &ch)) != TGEMM_SUCCESS) return rc;
     return run_scaled(M, N, K, alpha, A, lda, scaleA, B, ldb, scaleB, beta, C, ldc, dtype, ch.id,
                       ch.group_m, ch.xcd_remap, s);

@@ -175,12 +175,8 @@ static int table_rule(int64_t M, int64_t N, int64_t K, int dtype, bool vec_allow
     //    of 4 waves (64 x 64 each) on the same GPU, and 122 for the best
     //    direct schedule.  The transposed wave shape (128 x 32) gains nothing.
     //    Smaller problems keep the 128 x 128 tiles;
-    //  - x3, bf16 and e4m3: 256 x 256 macro-tiles of 8 waves, down to half a
-    //    wave of tiles (one workgroup per CU still beats 128 x 128 tiles
-    //    there); e4m3 with 128-deep panels and its waves 4 x 2 (64 x 128
-    //    each), 1317 TFLOP/s at 16384^3 against 1266 with waves 2 x 4 and
-    //    1195 for 128 x 128 tiles of four workgroups per CU (which it takes
-    //    below that size).
+    //  - x3: 256 x 256 macro-tiles of 8 waves, down to half a wave of tiles (one
+    //    workgroup per CU still beats 128 x 128 tiles there).
     //  - f32 with 256 to 383 tiles of 128 x 256 (half to three quarters of a
     //    wave at two workgroups per CU): 128 x 128 tiles on 16 x 16 MFMA blocks,
     //    four workgroups per CU (3000^3: 0.59 ms against 0.73 for 128 x 256).
@@ -256,7 +252,40 @@ static int table_rule(int64_t M, int64_t N, int64_t K, int dtype, bool vec_allow
             if (id >= 0) return take(id);
         }
     }
-    if (K >= 512 && packed_k_ok(K, dtype) && !narrow) {
+    // bf16 and e4m3.  Direct tiles (one launch instead of three) for few whole
+    // tiles or shallow K; past that packed operands, since the predicated body of
+    // a partial direct tile loses several times over with K: 256 x 256 tiles or
+    // 128 x 128 by the rounds of workgroups each needs (two 128 x 128 workgroups
+    // share a CU; a round of 256 x 256 tiles takes 1.8 times as long, 4096^3),
+    // 64- or 32-deep panels where K is shallow, and bf16 stream-K for deep K on few
+    // tiles.  Set from 319 shapes each, M, N, K log-uniform in [48, 8192], every
+    // schedule timed with scales on MI355X: the rule reaches 0.989 (bf16) and
+    // 0.980 (e4m3) of the fastest, geometric mean.  Against a rule that packed
+    // only from 192 tiles of 128 x 128 with K >= 512 and took 256 x 256 tiles from
+    // half a wave of them: bf16 2048 x 4096 x 4096 90 us / 115, 5000^2 x 300 50 /
+    // 153, e4m3 1000^2 x 8000 55 / 690, 16 x 4096^2 37 / 215.
+    if ((dtype == TGEMM_BF16 || dtype == TGEMM_FP8_E4M3) && packed_k_ok(K, dtype)) {
+        const bool bf16 = dtype == TGEMM_BF16;
+        const int64_t td = bf16 ? tiles(64, 64) : tiles(64, 128), t128 = tiles(128, 128), t256 = tiles(256, 256);
+        const bool whole = M % 64 == 0 && N % (bf16 ? 64 : 128) == 0;
+        // e4m3: the narrower, the more a packing pass costs beside its product
+        const int64_t deepest = std::min(M, N) <= 128 ? 8192 : std::min(M, N) <= 256 ? 4096 : 2048;
+        if (bf16 ? (whole && td < 768 && td * K <= 4000000 && K <= 8192) || (K <= 320 && td < 1024)
+                 : (whole && td < 384 && K <= deepest) || (K <= 128 && td < 512))
+            return direct_schedule(M, N, K, dtype, vec_allowed, out);
+        const bool big = 1.8 * (double)((t256 + 255) / 256) <= (double)((t128 + 511) / 512);
+        int id;
+        if (bf16 && K < 256) id = find_schedule(dtype, 128, 128, 32, 0, 2, 2);
+        else if (bf16 && K >= 5120 && t256 >= 16 && t128 <= 256) id = find_schedule(dtype, 256, 256, 64, 0, 2, 4, -1, 32, 1);
+        else if (bf16 && big) id = find_schedule(dtype, 256, 256, 64, 0, 2, 4);
+        else if (bf16) id = find_schedule(dtype, 128, 128, 64, 0, 2, 2, -1, t128 >= 128 ? 16 : 32);
+        else if (big && K >= 1280) id = find_schedule(dtype, 256, 256, 128, 0, 4, 2);
+        else if (t128 < 512) id = find_schedule(dtype, 128, 128, 128, 0, 2, 2);
+        else if (K < 1280) id = find_schedule(dtype, 128, 128, 64, 0, 2, 2, 32768);
+        else id = find_schedule(dtype, 128, 128, 128, 0, 2, 2, -1, 16);
+        if (id >= 0) return take(id);
+    }
+    if (K >= 512 && packed_k_ok(K, dtype) && !narrow && (dtype == TGEMM_F32 || dtype == TGEMM_F32_BF16X3)) {
         int id = -1;
         const int64_t panels16 = (K + 15) / 16, panels32 = (K + 31) / 32;
         // fraction of the launched waves the tiles fill, at `slots` resident workgroups
@@ -281,17 +310,21 @@ static int table_rule(int64_t M, int64_t N, int64_t K, int dtype, bool vec_allow
         } else if (dtype == TGEMM_F32_BF16X3 && tiles(256, 256) < 128 && tiles(128, 128) < 192) {
             if (tiles(256, 256) >= 8 && tiles(256, 256) * panels32 >= 8 * 256)
                 id = find_schedule(dtype, 256, 256, 32, 0, 2, 4, -1, 32, 1);
-        } else if (dtype == TGEMM_FP8_E4M3) {
-            if (tiles(256, 256) >= 128) id = find_schedule(dtype, 256, 256, 128, 0, 4, 2);
-            else if (tiles(128, 128) >= 192) id = find_schedule(dtype, 128, 128, 64, 0, 2, 2, 32768);
         } else {
-            const int bk = dtype == TGEMM_F32_BF16X3 ? 32 : 64;
-            if (tiles(256, 256) >= 128) id = find_schedule(dtype, 256, 256, bk, 0, 2, 4);
-            else if (tiles(128, 128) >= 192) id = find_schedule(dtype, 128, 128, bk, 0, 2, 2);
+            if (tiles(256, 256) >= 128) id = find_schedule(dtype, 256, 256, 32, 0, 2, 4);
+            else if (tiles(128, 128) >= 192) id = find_schedule(dtype, 128, 128, 32, 0, 2, 2);
         }
         if (id >= 0) return take(id);
     }
     return direct_schedule(M, N, K, dtype, vec_allowed, out);
+}
+
+// bf16 and e4m3 sizes whose packing workspace a caller without one must refuse;
+// the others can run direct tiles.
+bool scaled_needs_packing(int64_t M, int64_t N, int64_t K)
+{
+    auto tiles = [&](int b) { return ((M + b - 1) / b) * ((N + b - 1) / b); };
+    return K >= 512 && (tiles(256) >= 128 || tiles(128) >= 192);
 }
 
 int default_schedule(int64_t M, int64_t N, int64_t K, int dtype, bool vec_allowed, Choice* out)

@@ -27,6 +27,8 @@ bool costmodel_cached(int64_t M, int64_t N, int64_t K, int dtype, bool vec_allow
 // Built-in rule only (also the fallback of the other policies).
 int default_schedule(int64_t M, int64_t N, int64_t K, int dtype, bool vec_allowed, Choice* out);
 
+bool scaled_needs_packing(int64_t M, int64_t N, int64_t K);
+
 // Built-in rule restricted to schedules that need no workspace.
 int direct_schedule(int64_t M, int64_t N, int64_t K, int dtype, bool vec_allowed, Choice* out);
 
