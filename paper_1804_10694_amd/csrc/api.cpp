@@ -211,9 +211,8 @@ int tgemm(int64_t M, int64_t N, int64_t K, float alpha, const void* A, int64_t l
         return launch_scale_c((int)M, (int)N, beta, C, ldc, s) == hipSuccess ? TGEMM_SUCCESS
                                                                              : TGEMM_LAUNCH_FAILED;
     Choice ch;
-    const bool capturing = stream_capturing(s);
     const bool vok = vec_ok(A, lda, B, ldb, dtype);
-    rc = select_schedule(M, N, K, dtype, vok, &ch, !capturing);
+    rc = select_schedule(M, N, K, dtype, vok, &ch, policy_runs_model() && !stream_capturing(s));
     if (rc != TGEMM_SUCCESS) return rc;
     for (int attempt = 0; attempt < 2; ++attempt) {
         if (dtype == TGEMM_BF16 || dtype == TGEMM_FP8_E4M3)  // unscaled: every scale is 1
@@ -270,9 +269,8 @@ int tgemm_scaled(int64_t M, int64_t N, int64_t K, float alpha, const void* A, in
         return launch_scale_c((int)M, (int)N, beta, C, ldc, s) == hipSuccess ? TGEMM_SUCCESS
                                                                              : TGEMM_LAUNCH_FAILED;
     Choice ch;
-    const bool capturing = stream_capturing(s);
     const bool vok = vec_ok(A, lda, B, ldb, dtype);
-    rc = select_schedule(M, N, K, dtype, vok, &ch, !capturing);
+    rc = select_schedule(M, N, K, dtype, vok, &ch, policy_runs_model() && !stream_capturing(s));
     if (rc != TGEMM_SUCCESS) return rc;
     rc = run_scaled(M, N, K, alpha, A, lda, scaleA, B, ldb, scaleB, beta, C, ldc, dtype, ch.id,
                     ch.group_m, ch.xcd_remap, s);

@@ -334,6 +334,12 @@ int default_schedule(int64_t M, int64_t N, int64_t K, int dtype, bool vec_allowe
     return rc;
 }
 
+bool policy_runs_model()
+{
+    std::lock_guard<std::mutex> lk(g_sel_mu);
+    return g_policy == POLICY_MODEL;
+}
+
 int select_schedule(int64_t M, int64_t N, int64_t K, int dtype, bool vec_allowed, Choice* out,
                     bool may_run_model)
 {

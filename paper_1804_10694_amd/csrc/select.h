@@ -20,6 +20,10 @@ struct Choice {
 int select_schedule(int64_t M, int64_t N, int64_t K, int dtype, bool vec_allowed, Choice* out,
                     bool may_run_model = true);
 
+// Whether the current policy may run the cost model (only then does a call need
+// to know if its stream is being captured before it selects).
+bool policy_runs_model();
+
 // Cost-model answers for the "model" policy (false: no model, out of range).
 bool costmodel_choose(int64_t M, int64_t N, int64_t K, int dtype, bool vec_allowed, Choice* out);
 bool costmodel_cached(int64_t M, int64_t N, int64_t K, int dtype, bool vec_allowed, Choice* out);

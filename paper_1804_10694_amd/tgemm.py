@@ -111,8 +111,15 @@ def _dtype_code(dtype):
     return int(dtype)
 
 
+# The current stream's handle without a Stream object around it: 0.3 us against 2.7 us, of the
+# 9.9 us a small gemm call took on the host (its kernel takes 4.2 us on MI355X).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_handle(stream):
     if stream is None:
+        if _raw_stream is not None:
+            return _raw_stream(torch.cuda.current_device())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream
@@ -130,28 +137,33 @@ def _mat(t, name, elem=None):
         raise ValueError(f"{name} must be a GPU tensor")
     if t.dim() != 2:
         raise ValueError(f"{name} must be 2-D")
-    if t.shape[1] > 1 and t.stride(1) != 1:
+    rows, cols = t.shape
+    ld, unit = t.stride()
+    if unit != 1 and cols > 1:
         raise ValueError(f"{name} must have unit column stride (row-major)")
     if elem is not None and t.dtype != elem:
         if not (elem == torch.uint16 and t.dtype in (torch.bfloat16, torch.int16)):
             if not (elem == torch.uint8 and t.dtype in (torch.float8_e4m3fn, torch.int8)):
                 raise ValueError(f"{name} has dtype {t.dtype}, expected {elem}")
-    ld = t.stride(0) if t.shape[0] > 1 else max(t.shape[1], 1)
-    return t.data_ptr(), max(ld, 1)
+    if rows <= 1:
+        ld = cols
+    return t.data_ptr(), ld if ld > 1 else 1
 
 
 def gemm(A, B, C, alpha=1.0, beta=0.0, dtype="f32", stream=None):
     """C = alpha*A@B + beta*C in place (tgemm)."""
     dt = _dtype_code(dtype)
     M, K = A.shape
-    N = B.shape[1]
-    if B.shape[0] != K or tuple(C.shape) != (M, N):
+    Kb, N = B.shape
+    if Kb != K or C.shape != (M, N):
         raise ValueError(f"shape mismatch {tuple(A.shape)} @ {tuple(B.shape)} -> {tuple(C.shape)}")
-    pa, lda = _mat(A, "A", _ELEM.get(dt))
-    pb, ldb = _mat(B, "B", _ELEM.get(dt))
+    elem = _ELEM.get(dt)
+    pa, lda = _mat(A, "A", elem)
+    pb, ldb = _mat(B, "B", elem)
     pc, ldc = _mat(C, "C", torch.float32)
-    _check(lib.tgemm(M, N, K, alpha, pa, lda, pb, ldb, beta, pc, ldc, dt, _stream_handle(stream)),
-           "tgemm")
+    rc = lib.tgemm(M, N, K, alpha, pa, lda, pb, ldb, beta, pc, ldc, dt, _stream_handle(stream))
+    if rc:
+        raise TgemmError(rc, "tgemm")
     return C
 
 
