@@ -165,7 +165,8 @@ static bool no_room(int rc, int dtype, int64_t M, int64_t N, int64_t K)
 }
 
 // A float32 problem as the selection chose: on a register tile where the rule
-// names one that serves the operands, else on the schedule.
+// names one that serves the operands, else on the schedule; a stream-K form that
+// cannot have its workspace gives way to the schedule it was chosen over.
 int run_choice(const Choice& ch, int64_t M, int64_t N, int64_t K, float alpha, const void* A, int64_t lda,
                const void* B, int64_t ldb, float beta, float* C, int64_t ldc, int dtype, hipStream_t stream)
 {
@@ -175,7 +176,10 @@ int run_choice(const Choice& ch, int64_t M, int64_t N, int64_t K, float alpha, c
                                ch.xcd_remap, stream);
         if (rc != TGEMM_NOT_SUPPORTED) return rc;
     }
-    return run_gemm(ch.id, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, ch.group_m, ch.xcd_remap, stream);
+    const int rc = run_gemm(ch.id, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, ch.group_m, ch.xcd_remap, stream);
+    if (ch.unshared < 0 || (rc != TGEMM_CAPTURE_UNPLANNED && rc != TGEMM_ALLOC_FAILED && rc != TGEMM_NOT_SUPPORTED))
+        return rc;
+    return run_gemm(ch.unshared, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, ch.group_m, ch.xcd_remap, stream);
 }
 
 }  // namespace tg
@@ -223,7 +227,7 @@ int tgemm(int64_t M, int64_t N, int64_t K, float alpha, const void* A, int64_t l
         // a packed schedule whose workspace would have to grow under capture, or an
         // in-place one whose rows lie past the reach of its buffer offsets: use the
         // rule's schedule without packing instead
-        if (rc != TGEMM_CAPTURE_UNPLANNED && !(rc == TGEMM_NOT_SUPPORTED && schedule(ch.id).inplace) &&
+        if (rc != TGEMM_CAPTURE_UNPLANNED && !(rc == TGEMM_NOT_SUPPORTED && (schedule(ch.id).inplace || ch.unshared >= 0)) &&
             !no_room(rc, dtype, M, N, K))
             return rc;
         if ((rc = direct_schedule(M, N, K, dtype, vok, &ch)) != TGEMM_SUCCESS) return rc;

@@ -94,25 +94,33 @@ __global__ void __launch_bounds__(CF::NT, CF::WAVES_PER_EU) packed_kernel(Packed
     packed_tile<CF>(a, tc.tm * CF::BM, tc.tn * CF::BN, lds);
 }
 
-// Stream-K: the iterations (tile t, K panel p), numbered t * panels + p with
-// tiles in the grouped order of map_tile, are split into `grid` contiguous,
-// nearly equal ranges, one per workgroup of a single resident wave, so no
-// workgroup idles in a last partial wave of tiles.  A tile covered by several
-// ranges is summed by whichever of its workgroups finishes last: each writes
-// its partial sums to its own slot of `ws` and counts itself in cnt[t]; the
-// last one adds the partials in K order (so the result does not depend on
-// which workgroup that is) and writes C.  Nothing waits on another workgroup.
-// The partials are written and read with device-scope (agent) atomic stores
-// and loads, which are coherent across the XCDs' L2 caches on their own; a
-// device-scope fence would instead write back and invalidate the whole L2 of
-// the XCD, and with it the panels the other tiles there are reading.
+// Stream-K: one resident wave of `grid` workgroups.  Each first computes the
+// tiles of `rounds` whole rounds; the iterations (tile t, K panel p) of the tiles
+// left, numbered t * panels + p with tiles in the grouped order of map_tile, are
+// split into `grid` contiguous, nearly equal ranges, one per workgroup, so none
+// idles in a last partial round.  A tile covered by several ranges is summed by
+// whichever of its workgroups finishes last: the others write their partial sums
+// to their own slots of `ws` and count themselves in cnt[t]; the last one adds the
+// partials in K order, its own from its registers (so the result does not depend
+// on which workgroup that is), and writes C.  Nothing waits on another workgroup.
+// The partials are written and read with the device-scope (agent) cache policy,
+// coherent across the XCDs' L2 caches on its own; a device-scope fence would
+// instead write back and invalidate the whole L2 of the XCD, and with it the
+// panels the other tiles there are reading.
+//
+// The exchange of sums is what this form pays (256 KB per range of a 256 x 256
+// tile, all ranges at about the same time).  With every tile in the ranges, every
+// partial written, read back and in 4-byte accesses it took 712 us for x3 at 4500^3
+// (324 tiles), 422 at 5000^2 x 2000 and 1028 at 7000 x 5000 x 4000; in this form
+// 509, 299 and 712 (whole tiles: 586, 287, 796), f32 4753 x 4474 x 6243 1964
+// against 2250 in place.
 struct SkArgs {
     float* ws;   // 2 * grid slots of BM * BN floats: a range's first and last tile
     int* cnt;    // per-tile arrival counts; zero before and after every launch
-    int total;   // tiles * panels (< 2^31)
-    int grid;    // workgroups; every one has at least one iteration (grid <= total)
+    int rounds;  // tiles each workgroup computes whole before its range
+    int grid;    // workgroups
     int panels;  // K panels per tile
-    int q, r;    // total = q * grid + r: ranges 0 .. r-1 hold q + 1 iterations, the others q
+    int q, r;    // iterations of the ranges = q * grid + r: ranges 0 .. r-1 hold q + 1, the others q
 };
 
 __device__ __forceinline__ int sk_begin(const SkArgs& k, int v) { return v * k.q + min(v, k.r); }
@@ -141,12 +149,12 @@ struct SkPartial {
         return k.ws + (int64_t)(2 * u + (first ? 0 : 1)) * (CF::BM * CF::BN);
     }
 
-    // Sum r of block (i, j) of this lane in a slot: the 64 lanes of a wave hold
-    // 64 consecutive floats, so each (device-scope, 4-byte) store or load of a
-    // wave covers 256 contiguous bytes, and sum r + 1 follows 256 bytes later.
-    __device__ __forceinline__ static int elem(int wave, int i, int j, int r, int lane)
+    // Block (i, j) of a wave in a slot: four sums of each of its 64 lanes (one
+    // device-scope 16-byte store or load, 1 KB of the wave), then the next four.
+    __device__ __forceinline__ __amdgpu_buffer_rsrc_t block(int u, int wave, int i, int j) const
     {
-        return (((wave * CF::TM + i) * CF::TN + j) * CF::AR + r) * 64 + lane;
+        return __builtin_amdgcn_make_buffer_rsrc(
+            slot(u) + ((wave * CF::TM + i) * CF::TN + j) * CF::AR * 64, 0, CF::AR * 64 * 4, 0x00020000);
     }
 
     template <class SC>
@@ -155,29 +163,33 @@ struct SkPartial {
     {
         asm volatile("" : "+v"(lane));  // keep the slot addresses out of the main loop
         const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-        float* mine = slot(v);
-#pragma unroll
-        for (int i = 0; i < CF::TM; ++i)
-#pragma unroll
-            for (int j = 0; j < CF::TN; ++j) {
-                const float f = sc(i, j);
-#pragma unroll
-                for (int r = 0; r < CF::AR; ++r)
-                    __hip_atomic_store(mine + elem(wave, i, j, r, lane), f * acc[i][j][r], __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
-            }
         const int u0 = sk_owner(k, t * k.panels), u1 = sk_owner(k, (t + 1) * k.panels - 1);
-        __builtin_amdgcn_s_waitcnt(0);  // this thread's partial stores have completed ...
-        __syncthreads();                // ... and every thread's: the partial is complete
-        if (threadIdx.x == 0) {
-            const int last = atomicAdd(&k.cnt[t], 1) == u1 - u0;
-            // every range has arrived: the counter is ready for the next launch
-            if (last) __hip_atomic_store(&k.cnt[t], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            *flag = last;
-        }
+        if (threadIdx.x == 0) *flag = __hip_atomic_load(&k.cnt[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == u1 - u0;
         __syncthreads();
-        if (!*flag) return;
-        // sum every range's partial (this one's included, read back) in K order,
+        if (!__builtin_amdgcn_readfirstlane(*flag)) {
+#pragma unroll
+            for (int i = 0; i < CF::TM; ++i)
+#pragma unroll
+                for (int j = 0; j < CF::TN; ++j) {
+                    const float f = sc(i, j);
+                    const __amdgpu_buffer_rsrc_t rs = block(v, wave, i, j);
+#pragma unroll
+                    for (int r = 0; r < CF::AR; r += 4) {
+                        u32x4 x;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) x[e] = __float_as_uint(f * acc[i][j][r + e]);
+                        __builtin_amdgcn_raw_buffer_store_b128(x, rs, lane * 16 + r * 256, 0, kSc1);
+                    }
+                }
+            __builtin_amdgcn_s_waitcnt(0);  // this thread's partial stores have completed ...
+            __syncthreads();                // ... and every thread's: the partial is complete
+            if (threadIdx.x == 0) *flag = atomicAdd(&k.cnt[t], 1) == u1 - u0;
+            __syncthreads();
+            if (!__builtin_amdgcn_readfirstlane(*flag)) return;
+        }
+        // every range has arrived: the counter is ready for the next launch
+        if (threadIdx.x == 0) __hip_atomic_store(&k.cnt[t], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        // sum every range's partial (this one's from its registers) in K order,
         // FB blocks at a time: for each slot, the loads of all FB blocks go out
         // together (one uniform range per block, the lane's offset, r * 256
         // bytes as the instruction's offset), with the device-scope cache
@@ -193,21 +205,28 @@ struct SkPartial {
 #pragma unroll
                 for (int r = 0; r < CF::AR; ++r) s[q][r] = 0.f;
             for (int u = u0; u <= u1; ++u) {
-                const float* src = slot(u);
-                float x[FB][CF::AR];
+                if (u == v) {
+#pragma unroll
+                    for (int q = 0; q < FB; ++q) {
+                        const int i = (b0 + q) / CF::TN, j = (b0 + q) % CF::TN;
+                        const float f = sc(i, j);
+#pragma unroll
+                        for (int r = 0; r < CF::AR; ++r) s[q][r] += f * acc[i][j][r];
+                    }
+                    continue;
+                }
+                u32x4 x[FB][CF::AR / 4];
 #pragma unroll
                 for (int q = 0; q < FB; ++q) {
-                    const int i = (b0 + q) / CF::TN, j = (b0 + q) % CF::TN;
-                    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-                        const_cast<float*>(src) + elem(wave, i, j, 0, 0), 0, CF::AR * 64 * 4, 0x00020000);
+                    const __amdgpu_buffer_rsrc_t rs = block(u, wave, (b0 + q) / CF::TN, (b0 + q) % CF::TN);
 #pragma unroll
-                    for (int r = 0; r < CF::AR; ++r)
-                        x[q][r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, lane * 4 + r * 256, 0, kSc1));
+                    for (int r = 0; r < CF::AR; r += 4)
+                        x[q][r / 4] = __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16 + r * 256, 0, kSc1);
                 }
 #pragma unroll
                 for (int q = 0; q < FB; ++q)
 #pragma unroll
-                    for (int r = 0; r < CF::AR; ++r) s[q][r] += x[q][r];
+                    for (int r = 0; r < CF::AR; ++r) s[q][r] += __uint_as_float(x[q][r / 4][r % 4]);
             }
             write_c<1, FB, CF::AR>(
                 a.C, a.ldc, a.M, a.N, a.beta, CF::out_row(0, lane), CF::out_col(lane),
@@ -252,11 +271,13 @@ __global__ void __launch_bounds__(CF::NT, CF::WAVES_PER_EU) packed_sk_kernel(Pac
     using AL = typename TileParts<CF>::A;
     using BL = typename TileParts<CF>::B;
     using OP = typename TileParts<CF>::Op;
-    for (int it = sk_begin(k, v); it < end;) {
-        const int t = it / k.panels;
-        const int pb = it - t * k.panels;
-        const int pe = min(k.panels, pb + (end - it));
-        const TileCoord tc = map_tile(t, a.tiles_m, a.tiles_n, a.group_m, 0);
+    const int whole = k.rounds * k.grid;  // tiles whole .. of the order are shared out in ranges
+    for (int n = 0, it = sk_begin(k, v); n < k.rounds || it < end; ++n) {
+        const bool all = n < k.rounds;
+        const int t = all ? 0 : it / k.panels;
+        const int pb = all ? 0 : it - t * k.panels;
+        const int pe = all ? k.panels : min(k.panels, pb + (end - it));
+        const TileCoord tc = map_tile(all ? n * k.grid + v : whole + t, a.tiles_m, a.tiles_n, a.group_m, 0);
         const int m0 = tc.tm * CF::BM, n0 = tc.tn * CF::BN;
         const SkStore<CF> epi{TileStore<CF>{a, m0, n0}, SkPartial<CF>{a, k, t, v, m0, n0, &flag},
                               pb == 0 && pe == k.panels};
@@ -264,7 +285,7 @@ __global__ void __launch_bounds__(CF::NT, CF::WAVES_PER_EU) packed_sk_kernel(Pac
             packed_tile_range<CF, AL, BL, OP, true>(a, m0, n0, lds, typename AL::Geom(), pb, pe - pb, epi);
         else
             packed_tile_range<CF, AL, BL, OP, false>(a, m0, n0, lds, typename AL::Geom(), pb, pe - pb, epi);
-        it += pe - pb;
+        if (!all) it += pe - pb;
         __syncthreads();  // every wave is done with the LDS stages (and the flag) before the next tile
     }
 }
@@ -620,6 +641,16 @@ bool packed_k_ok(int64_t K, int dtype)
     return kPackRows * packed_kp(K, es) * es <= INT32_MAX;
 }
 
+// Rounds of whole tiles before the ranges of a stream-K launch: all of them, but
+// where less than a sixteenth of a round is left one fewer, as one workgroup would
+// have to add more than 16 partials (289 tiles of x3, K 1024, about 8 ranges a tile:
+// 152 us; with the last whole round in the ranges too, 161).
+int sk_rounds(int tiles, int grid)
+{
+    const int full = tiles / grid, rest = tiles - full * grid;
+    return full - (full > 0 && rest > 0 && 16 * rest < grid);
+}
+
 // pid < kNumPacked: one workgroup per tile.  pid >= kNumPacked: the stream-K
 // form of row g_sk_of[pid - kNumPacked], with its partial sums after the packed
 // operands in `ws` and the stream's counters `cnt`.
@@ -679,14 +710,15 @@ int run_packed_ws(int pid, int64_t M, int64_t N, int64_t K, float alpha, const v
         k.panels = (int)((K + bk - 1) / bk);
         const int64_t total = (int64_t)tiles * k.panels;
         if (tiles > kSkMaxTiles || total > INT32_MAX || !cnt) return TGEMM_NOT_SUPPORTED;
-        k.total = (int)total;
         const int slots = resident_slots(reinterpret_cast<const void*>(p.sk_kernel), p.threads);
         // whole XCD groups, and at least one iteration per workgroup
-        int grid = std::min(slots, k.total);
+        int grid = (int)std::min<int64_t>(slots, total);
         if (grid >= kNumXcd) grid -= grid % kNumXcd;
         k.grid = grid;
-        k.q = k.total / grid;
-        k.r = k.total % grid;
+        k.rounds = sk_rounds(tiles, grid);
+        const int shared = (tiles - k.rounds * grid) * k.panels;
+        k.q = shared / grid;
+        k.r = shared % grid;
         k.cnt = cnt;
         k.ws = reinterpret_cast<float*>(base + packed_workspace_bytes(M, N, K, p.dtype));
         a.group_m = group_m < 1 ? 1 : group_m;
@@ -761,6 +793,8 @@ extern "C" int tgemm_noalloc(int64_t M, int64_t N, int64_t K, float alpha, const
     Choice ch;
     const bool vok = vec_ok(A, lda, B, ldb, dtype);
     if ((rc = select_schedule(M, N, K, dtype, vok, &ch, false)) != TGEMM_SUCCESS) return rc;
+    if (ch.unshared >= 0) ch.id = ch.unshared;  // no counters, and no workspace for partial sums
+    ch.unshared = -1;
     const bool scaled = (dtype == TGEMM_BF16 || dtype == TGEMM_FP8_E4M3);
     const int pid = packed_index(ch.id);
     if (pid < 0) {  // direct and in-place schedules use no workspace

@@ -12,6 +12,7 @@ struct Choice {
     int xcd_remap;
     int reg = -1;  // register tile that runs the problem instead of the schedule where it can
                    // (set by the built-in rule only: the table's ids name LDS-pipeline schedules)
+    int unshared = -1;  // the rule's schedule where the stream-K form it chose finds no workspace
 };
 
 // Picks a schedule for the current policy; vec_allowed says whether the
