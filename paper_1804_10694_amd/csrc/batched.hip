@@ -267,7 +267,7 @@ __global__ void __launch_bounds__(256) small_batched_kernel(SmallArgs a)
         else acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, acc, 0, 0, 0);
     }
     constexpr int AR = T == 16 ? 4 : 16;
-    write_c<1, 1, AR>(
+    write_c<1, 1, AR, 16, T>(
         C, a.ldc, a.M, a.N, a.beta, (T == 16) ? 4 * (lane / 16) : 4 * (lane / 32), lane % T,
         [&](int, int, float (&v)[AR]) {
 #pragma unroll

@@ -23,7 +23,14 @@ namespace tg {
 // elements outside M x N read as zero and are never written, without a branch.
 // Offsets are 32-bit: with ldc >= 2^25 a plain per-element loop runs instead.
 // beta == 0 never reads C.
-template <int TM, int TN, int AR, int CH = 16, class Val, class Org, class RowOf>
+//
+// A chunk whose blocks (of H rows at most) end within M needs no range per row:
+// one resource per block, the row as the scalar offset (ldc < 2^24, so that it
+// stays below 2^31; the lanes past N keep their offset beyond the range).  What
+// that saves is vector instructions (64-bit compares for the ranges): beside a
+// wave that keeps the matrix core busy, each of them takes about as long as an
+// f32 MFMA (64 cycles), so the 64 stores of a 64 x 64 wave tile took 10 us.
+template <int TM, int TN, int AR, int CH = 16, int H = 32, class Val, class Org, class RowOf>
 __device__ __forceinline__ void write_c(float* C, int64_t ldc, int M, int N, float beta, int lane_row,
                                         int lane_col, const Val& val, const Org& origin, const RowOf& rrow)
 {
@@ -56,6 +63,7 @@ __device__ __forceinline__ void write_c(float* C, int64_t ldc, int M, int N, flo
         int64_t bytes[NB];
         int lo[NB];
         float v[NB][AR];
+        bool whole = ldc < (int64_t(1) << 24);
 #pragma unroll
         for (int q = 0; q < NB; ++q) {
             if (b0 + q >= NBLK) continue;
@@ -68,8 +76,39 @@ __device__ __forceinline__ void write_c(float* C, int64_t ldc, int M, int N, flo
             const int64_t left = (int64_t)(M - 1 - r0) * ldc + (N - c0);
             bytes[q] = r0 >= M || left <= 0 ? 0 : left * 4;
             base[q] = C + (int64_t)r0 * ldc + c0;
+            whole = whole && r0 + H <= M;
             lo[q] = (c0 + lane_col < N) ? lane_row * ldc4 + lane_col * 4 : (int)0x80000000u;
             val(i, j, v[q]);
+        }
+        if (whole) {
+            auto block = [&](int q) {
+                return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base[q]), 0, 0x7fffffff, 0x00020000);
+            };
+            if (beta != 0.f) {
+                float c[NB][AR];
+#pragma unroll
+                for (int q = 0; q < NB; ++q) {
+                    if (b0 + q >= NBLK) continue;
+#pragma unroll
+                    for (int r = 0; r < AR; ++r)
+                        c[q][r] = __uint_as_float(
+                            __builtin_amdgcn_raw_buffer_load_b32(block(q), lo[q], rrow(r) * ldc4, 0));
+                }
+#pragma unroll
+                for (int q = 0; q < NB; ++q) {
+                    if (b0 + q >= NBLK) continue;
+#pragma unroll
+                    for (int r = 0; r < AR; ++r) v[q][r] = fmaf(beta, c[q][r], v[q][r]);
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < NB; ++q) {
+                if (b0 + q >= NBLK) continue;
+#pragma unroll
+                for (int r = 0; r < AR; ++r)
+                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v[q][r]), block(q), lo[q], rrow(r) * ldc4, 0);
+            }
+            continue;
         }
         // value r of block q: the range from its row (a uniform base and
         // length), at the lane's offset, which is the same for every r

@@ -228,7 +228,7 @@ struct SkPartial {
 #pragma unroll
                     for (int r = 0; r < CF::AR; ++r) s[q][r] += __uint_as_float(x[q][r / 4][r % 4]);
             }
-            write_c<1, FB, CF::AR>(
+            write_c<1, FB, CF::AR, 16, CF::MS>(
                 a.C, a.ldc, a.M, a.N, a.beta, CF::out_row(0, lane), CF::out_col(lane),
                 [&](int, int q, float (&v)[CF::AR]) {
 #pragma unroll

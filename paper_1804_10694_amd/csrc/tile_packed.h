@@ -848,7 +848,7 @@ struct TileStore {
         // the addresses below are computed here, not hoisted out of a loop over
         // tiles where they would hold registers through the main loop
         asm volatile("" : "+v"(lane));
-        write_c<CF::TM, CF::TN, CF::AR>(
+        write_c<CF::TM, CF::TN, CF::AR, 16, CF::MS>(
             a.C, a.ldc, a.M, a.N, a.beta, CF::out_row(0, lane), CF::out_col(lane),
             [&](int i, int j, float (&v)[CF::AR]) {
                 const float f = a.alpha * sc(i, j);
