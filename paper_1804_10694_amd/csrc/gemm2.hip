@@ -5,18 +5,27 @@
 //   T = act(A B)                 A: M x K, B: K x N1 (N1 <= 256)
 //   E = alpha * T D + beta * E   D: N1 x N2, E: M x N2
 //
-// One workgroup owns 64 rows of the output.  Phase 1 computes its 64 x N1
-// block of T with the in-place pipeline of tile_inplace.h (K panels of A and B
-// straight from memory into LDS), applies act in registers and stores T into
-// LDS as N1/16 panels of 16 columns in the packed A layout; T never goes to
-// memory.  Phase 2 walks E's columns in chunks of 128: each chunk streams
-// 16-row panels of D into LDS while the MFMAs take their A operands from the
-// resident T panels, then writes alpha * acc + beta * E.  Phase 1's pipeline
-// stages live in the bytes T later takes, so a workgroup holds T plus two
-// 8 KB D stages: two workgroups per CU for N1 up to 256, three up to 128.  Columns of T at or
+// One workgroup of four waves owns 64 rows of the output (or 32, below).  Phase 1
+// computes its 64 x N1 block of T, a quarter of the columns per wave: 32-deep
+// panels of A go from memory into a ring in LDS, three ahead of the one being
+// read; B goes from L2 straight into each wave's registers, one panel ahead
+// (no other wave of the workgroup needs those columns).  act is applied in
+// registers and T stored into LDS as N1/32 panels in the layout of A's, over the
+// ring; T never goes to memory.  Phase 2 walks E's columns in chunks of 256 (or
+// 128), each wave with A operands from the resident T panels and its columns of D
+// in registers, without a barrier, then writes alpha * acc + beta * E.  A workgroup
+// holds T only: two per CU for N1 up to 256, three up to 128.  Columns of T at or
 // past N1 are stored as zero, so that nothing read past N1 (whatever B holds
 // there) can reach E.  T is kept in FP32; the x3 form splits it, like every
 // operand, into bf16 high and low parts when it reads it from LDS.
+//
+// What bounds it: the matrix cores (f32 at 98304 x 256 x 256 x 256: 167 us of MFMAs
+// in 198), and the waves of a CU reaching their epilogues together.  With B and D
+// through LDS in 16-deep panels, a barrier each, and E in chunks of 128 columns, f32
+// took 212 there and x3 114, now 93.  A workgroup alone on its CU takes 1.7 times
+// as long as its MFMAs, so the rows past the last whole round of workgroups go out in
+// 32s, and first, beside others: 100352 rows f32 236 -> 217 us, x3 130 -> 100;
+// 8192 x 1024 x 256 x 1024 f32 158 -> 83; 1000 rows 42 -> 24.
 #include <hip/hip_runtime.h>
 
 #include "../../include/tgemm.h"
@@ -37,22 +46,92 @@ struct G2Args {
     int M, N1, N2, K;
     float alpha, beta;
     int relu;
+    int tall;  // workgroups of 64 rows; those before them take 32 each of the rows left
 };
 
-template <int MODE, int N1P>
+template <int MODE, int N1P, int RB>
 struct G2Cfg {
-    static constexpr int BM = 64, BK = 16, NT = 256;
-    using P1 = ICfg<MODE, 64, N1P, 16, 1, 4, 2>;  // phase 1: a 64 x N1P block of T, 4 waves side by side
-    using P2 = ICfg<MODE, 64, 128, 16, 1, 4, 2>;  // phase 2: a 64 x 128 chunk of E
-    static constexpr int CHUNK = P2::BN;
-    static constexpr int TPANEL = 64 * 16 * 4;    // one 16-column panel of T (packed A layout, 4 units a row)
-    static constexpr int T_BYTES = (N1P / 16) * TPANEL;
-    static constexpr int LDS_BYTES = T_BYTES + 2 * P2::LDS_B;
-    static constexpr int WG_PER_CU = (160 * 1024) / LDS_BYTES;
-    static_assert(P1::LDS_BYTES <= T_BYTES, "phase-1 stages fit where T goes");
-    static_assert(P1::UK == 4 && P2::UK == 4, "T panels use the layout of 16-deep A panels");
-    static_assert(LDS_BYTES <= 160 * 1024, "LDS");
+    static constexpr int BK = 32, NT = 256, AHEAD = 3;
+    using P1 = ICfg<MODE, RB, N1P, BK, 1, 4, 2>;  // phase 1: an RB x N1P block of T, 4 waves side by side
+    template <int TN>
+    using P2 = ICfg<MODE, RB, 128 * TN, BK, 1, 4, 2>;  // phase 2: an RB x 128 TN chunk of E
+    static constexpr int PANEL = RB * BK * 4;  // one 32-column panel of A or T (8 units a row)
+    static constexpr int NPAN = N1P / BK;
+    static constexpr int LDS_BYTES = NPAN * PANEL;
+    static_assert(AHEAD < NPAN, "A panels in flight and the one being read fit where T goes");
 };
+
+// Rows of B or D from one on: what follows in bytes (0 past the last row or column).
+struct G2Src {
+    __amdgpu_buffer_rsrc_t r;
+    uint32_t row_bytes;
+};
+
+// Rows k0 .. k0 + BK of the columns from n0 on of a K x N matrix.
+template <int BK>
+__device__ __forceinline__ G2Src g2_rows(const char* base, int64_t ld, int K, int N, int k0, int n0)
+{
+    const int rows = min(BK, K - k0), cols = N - n0;
+    const bool any = rows > 0 && cols > 0;
+    const uint32_t row_bytes = (uint32_t)ld * 4u;
+    return {make_rsrc(base + (any ? k0 * ld + n0 : 0) * 4,
+                      any ? (int)((uint32_t)(rows - 1) * row_bytes + (uint32_t)cols * 4u) : 0), row_bytes};
+}
+
+// One panel (BK rows) of B or D in registers, one 4-byte load per value: lane half h
+// holds rows MK g + HS h + e of group g, column 32 j + lane % 32 of the wave's columns.
+// The row goes into the buffer resource (scalar registers), not into lane offsets,
+// which the compiler would keep in 16 vector registers.
+template <class CF>
+struct G2Rows {
+    float v[CF::NG][CF::TN][CF::HS];
+
+    __device__ __forceinline__ void load_group(const G2Src& src, uint32_t at, int g)
+    {
+#pragma unroll
+        for (int e = 0; e < CF::HS; ++e) {
+            const uint32_t off = at + (uint32_t)(CF::MK * g + e) * src.row_bytes;
+#pragma unroll
+            for (int j = 0; j < CF::TN; ++j)
+                v[g][j][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(src.r, (int)(off + 128 * j), 0, 0));
+        }
+    }
+};
+
+// The MFMAs of group g: A operands as read from LDS, B operands from registers.
+template <class CF>
+__device__ __forceinline__ void g2_mma(const typename InplaceOps<CF>::Ops& oa, const G2Rows<CF>& b, int g,
+                                       f32x16 (&acc)[CF::TM][CF::TN])
+{
+    typename InplaceOps<CF>::Ops o = oa;
+#pragma unroll
+    for (int j = 0; j < CF::TN; ++j) {
+        if constexpr (CF::MODE == MODE_F32) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o.b[j][e] = b.v[g][j][e];
+        } else {
+            split_bf16x8(b.v[g][j], o.bh[j], o.bl[j]);
+        }
+    }
+    InplaceOps<CF>::compute(o, acc);
+}
+
+// One panel: A from LDS at `la`, B from registers, each group's registers refilled
+// from the next panel (through `next`) once its MFMAs have been issued.
+template <class CF>
+__device__ __forceinline__ void g2_panel(const char* la, G2Rows<CF>& b, const G2Src& next, uint32_t at,
+                                         f32x16 (&acc)[CF::TM][CF::TN], int lane)
+{
+    using OP = InplaceOps<CF>;
+    typename OP::Ops oa[2];
+    OP::load_a(la, oa[0], 0, 0, lane);
+#pragma unroll
+    for (int g = 0; g < CF::NG; ++g) {
+        if (g + 1 < CF::NG) OP::load_a(la, oa[(g + 1) & 1], g + 1, 0, lane);
+        g2_mma<CF>(oa[g & 1], b, g, acc);
+        b.load_group(next, at, g);
+    }
+}
 
 template <class CF>
 __device__ __forceinline__ void zero_acc(f32x16 (&acc)[CF::TM][CF::TN])
@@ -65,110 +144,29 @@ __device__ __forceinline__ void zero_acc(f32x16 (&acc)[CF::TM][CF::TN])
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 }
 
-template <int MODE, int N1P>
-constexpr int kG2Occ = G2Cfg<MODE, N1P>::WG_PER_CU;
-
-template <int MODE, int N1P, bool VEC>
-__global__ void __launch_bounds__(256, (kG2Occ<MODE, N1P>)) gemm2_kernel(G2Args g)
+// Phase 2: E[m0:m0+RB, :] = alpha * T D + beta * E in chunks of 128 TN columns, a
+// quarter per wave.  No barriers: T only is shared, and it stays.
+template <class G, int TN>
+__device__ __forceinline__ void g2_second(const G2Args& g, const char* tbuf, int m0, int wave, int lane)
 {
-    using G = G2Cfg<MODE, N1P>;
-    using P1 = typename G::P1;
-    using P2 = typename G::P2;
-    __shared__ __attribute__((aligned(1024))) char lds[G::LDS_BYTES];
-    char* tbuf = lds;                    // resident T panels (phase 1: its stages)
-    char* stages = lds;                  // phase-1 stages
-    char* dstages = lds + G::T_BYTES;    // phase-2 stages
-
-    const int t = threadIdx.x, lane = t & 63, h = lane >> 5, l32 = lane & 31;
-    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int m0 = blockIdx.x * G::BM;
-
-    // ---- phase 1: T block = act(A[m0:m0+64, :] B)
-    {
-        PackedArgs a{};
-        a.A = g.A;
-        a.lda = g.lda;
-        a.B = g.B;
-        a.ldb = g.ldb;
-        a.M = g.M;
-        a.N = g.N1;
-        a.K = g.K;
-        InplaceA<P1, VEC> al;
-        al.init(a, m0, lane, wave, typename InplaceA<P1, VEC>::Geom());
-        InplaceB<P1, VEC> bl;
-        bl.init(a, 0, lane, wave);
-        const int wn0 = wave * P1::WTN;
-        f32x16 acc[P1::TM][P1::TN];
-        zero_acc<P1>(acc);
-        const int npanel = (g.K + G::BK - 1) / G::BK;
-        al.issue(0, stages);
-        bl.issue(0, stages + P1::LDS_A);
-        for (int s = 0; s < npanel; ++s) {
-            wait_vmcnt<0>();
-            lds_barrier();
-            if (s + 1 < npanel) {
-                char* st = stages + ((s + 1) & 1) * P1::LDS_STAGE;
-                al.issue(s + 1, st);
-                bl.issue(s + 1, st + P1::LDS_A);
-            }
-            pk_mma<P1, InplaceOps<P1>>(stages + (s & 1) * P1::LDS_STAGE, acc, 0, wn0, lane);
-        }
-        // act(acc) -> T panels, over the phase-1 stages once every wave is done
-        // with them; columns at or past N1 become zero
-        wait_lds_reads();
-        lds_barrier();
-#pragma unroll
-        for (int i = 0; i < P1::TM; ++i)
-#pragma unroll
-            for (int j = 0; j < P1::TN; ++j)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int row = 32 * i + 8 * (r >> 2) + 4 * h + (r & 3);
-                    const int col = wn0 + 32 * j + l32;
-                    float v = acc[i][j][r];
-                    if (g.relu && v < 0.f) v = 0.f;  // max(v, 0); NaN stays NaN
-                    if (col >= g.N1) v = 0.f;
-                    *reinterpret_cast<float*>(tbuf + (col / 16) * G::TPANEL +
-                                              pk_slot<4>(row, (col % 16) / 4) * 16 + (col % 4) * 4) = v;
-                }
-        __syncthreads();  // T complete and visible to every wave
-    }
-
-    // ---- phase 2: E[m0:m0+64, n0:n0+128] = alpha * T D[:, n0:n0+128] + beta * E
-    PackedArgs d{};
-    d.B = g.D;
-    d.ldb = g.ldd;
-    d.N = g.N2;
-    d.K = g.N1;
+    using P2 = typename G::template P2<TN>;
+    const int h = lane >> 5, l32 = lane & 31;
     const int wn0 = wave * P2::WTN;
     const int npanel = (g.N1 + G::BK - 1) / G::BK;
-    for (int n0 = 0; n0 < g.N2; n0 += G::CHUNK) {
-        InplaceB<P2, VEC> dl;
-        dl.init(d, n0, lane, wave);
+    const uint32_t at = (uint32_t)(P2::HS * h) * (uint32_t)g.ldd * 4u + (uint32_t)l32 * 4u;
+    G2Rows<P2> b;
+    const G2Src first = g2_rows<G::BK>(g.D, g.ldd, g.N1, g.N2, 0, wn0);
+#pragma unroll
+    for (int q = 0; q < P2::NG; ++q) b.load_group(first, at, q);
+    for (int n0 = wn0; n0 < g.N2; n0 += P2::BN) {
         f32x16 acc[P2::TM][P2::TN];
         zero_acc<P2>(acc);
-        dl.issue(0, dstages);
         for (int s = 0; s < npanel; ++s) {
-            wait_vmcnt<0>();
-            lds_barrier();
-            if (s + 1 < npanel) dl.issue(s + 1, dstages + ((s + 1) & 1) * P2::LDS_B);
-            const char* ta = tbuf + s * G::TPANEL;
-            const char* lb = dstages + (s & 1) * P2::LDS_B;
-            using OP = InplaceOps<P2>;
-            typename OP::Ops ops[2];
-            OP::load_a(ta, ops[0], 0, 0, lane);
-            OP::load_b(lb, ops[0], 0, wn0, lane);
-#pragma unroll
-            for (int q = 0; q < P2::NG; ++q) {
-                if (q + 1 < P2::NG) {
-                    OP::load_a(ta, ops[(q + 1) & 1], q + 1, 0, lane);
-                    OP::load_b(lb, ops[(q + 1) & 1], q + 1, wn0, lane);
-                }
-                OP::compute(ops[q & 1], acc);
-            }
+            const bool last = s + 1 == npanel;  // the next chunk's first panel follows
+            g2_panel<P2>(tbuf + s * G::PANEL, b,
+                         g2_rows<G::BK>(g.D, g.ldd, g.N1, g.N2, last ? 0 : (s + 1) * G::BK, last ? n0 + P2::BN : n0),
+                         at, acc, lane);
         }
-        wait_lds_reads();
-        lds_barrier();  // every wave is done with the stages before the next chunk refills them
         write_c<P2::TM, P2::TN, 16>(
             g.E, g.lde, g.M, g.N2, g.beta, 4 * h, l32,
             [&](int i, int j, float (&v)[16]) {
@@ -177,10 +175,93 @@ __global__ void __launch_bounds__(256, (kG2Occ<MODE, N1P>)) gemm2_kernel(G2Args 
             },
             [&](int i, int j, int& r0, int& c0) {
                 r0 = m0 + 32 * i;
-                c0 = n0 + wn0 + 32 * j;
+                c0 = n0 + 32 * j;
             },
             [](int r) { return 8 * (r >> 2) + (r & 3); });
     }
+}
+
+template <int MODE, int N1P, int RB, bool VEC>
+__device__ __forceinline__ void g2_block(const G2Args& g, int m0, char* lds)
+{
+    using G = G2Cfg<MODE, N1P, RB>;
+    using P1 = typename G::P1;
+    const int t = threadIdx.x, lane = t & 63, h = lane >> 5, l32 = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+
+    // ---- phase 1: T block = act(A[m0:m0+RB, :] B)
+    {
+        PackedArgs a{};
+        a.A = g.A;
+        a.lda = g.lda;
+        a.M = g.M;
+        a.K = g.K;
+        InplaceA<P1, VEC> al;
+        al.init(a, m0, lane, wave, typename InplaceA<P1, VEC>::Geom());
+        const int wn0 = wave * P1::WTN;
+        const int npanel = (g.K + G::BK - 1) / G::BK;
+        const uint32_t at = (uint32_t)(P1::HS * h) * (uint32_t)g.ldb * 4u + (uint32_t)l32 * 4u;
+        for (int s = 0; s < G::AHEAD && s < npanel; ++s) al.issue(s, lds + s * G::PANEL);
+        G2Rows<P1> b;
+        const G2Src first = g2_rows<G::BK>(g.B, g.ldb, g.K, g.N1, 0, wn0);
+#pragma unroll
+        for (int q = 0; q < P1::NG; ++q) b.load_group(first, at, q);
+        f32x16 acc[P1::TM][P1::TN];
+        zero_acc<P1>(acc);
+        wait_vmcnt<0>();
+        for (int s = 0; s < npanel; ++s) {
+            // A panel s was issued at panel s - 3 (or before the wait above), and the
+            // panels since issued more loads of B than may be in flight here
+            constexpr int FLIGHT = P1::NG * P1::HS * P1::TN;
+            wait_vmcnt<FLIGHT>();
+            wait_lds_reads();  // of panel s - 1, whose stage may be refilled from here on
+            lds_barrier();
+            if (s + G::AHEAD < npanel) al.issue(s + G::AHEAD, lds + (s + G::AHEAD) % G::NPAN * G::PANEL);
+            g2_panel<P1>(lds + s % G::NPAN * G::PANEL, b,
+                         g2_rows<G::BK>(g.B, g.ldb, g.K, g.N1, (s + 1) * G::BK, wn0), at, acc, lane);
+        }
+        // act(acc) -> T panels, over the A panels once every wave is done with
+        // them; columns at or past N1 become zero
+        wait_lds_reads();
+        lds_barrier();
+        const bool pad = wn0 + P1::WTN > g.N1;
+#pragma unroll
+        for (int j = 0; j < P1::TN; ++j) {
+            // block j's columns are one T panel; row 32 i + 8 (r / 4) + 4 h + r % 4 of column
+            // l32 is unit l32 / 4, XORed as pk_slot<8> has it with row / 2 =
+            // 4 (r / 4) + 2 h + (r % 4) / 2, mod 8
+            const int col = (wn0 / 32 + j) * G::PANEL + 4 * h * 128 + ((l32 / 4) ^ (2 * h)) * 16 + (l32 % 4) * 4;
+            const bool out = wn0 + 32 * j + l32 >= g.N1;
+#pragma unroll
+            for (int i = 0; i < P1::TM; ++i) {
+                f32x16 v = acc[i][j];
+                if (g.relu)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) v[r] = v[r] < 0.f ? 0.f : v[r];  // max(v, 0); NaN stays NaN
+                if (pad)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) v[r] = out ? 0.f : v[r];
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int flip = (4 * (r >> 2) + ((r & 3) >> 1)) & 7;
+                    *reinterpret_cast<float*>(lds + (col ^ (flip * 16)) + (32 * i + 8 * (r >> 2) + (r & 3)) * 128) = v[r];
+                }
+            }
+        }
+        __syncthreads();  // T complete and visible to every wave
+    }
+
+    if (N1P == 128 || ((g.N2 + 127) / 128 & 1)) g2_second<G, 1>(g, lds, m0, wave, lane);
+    else g2_second<G, 2>(g, lds, m0, wave, lane);
+}
+
+template <int MODE, int N1P, bool VEC>
+__global__ void __launch_bounds__(256, (N1P == 128 ? 3 : 2)) gemm2_kernel(G2Args g)
+{
+    __shared__ __attribute__((aligned(1024))) char lds[G2Cfg<MODE, N1P, 64>::LDS_BYTES];  // A panels in turn, then T
+    const int low = gridDim.x - g.tall, wg = blockIdx.x;
+    if (wg < low) g2_block<MODE, N1P, 32, VEC>(g, 64 * g.tall + 32 * wg, lds);
+    else g2_block<MODE, N1P, 64, VEC>(g, 64 * (wg - low), lds);
 }
 
 namespace {
@@ -246,7 +327,11 @@ extern "C" int tgemm_gemm2(int64_t M, int64_t N1, int64_t N2, int64_t K, float a
     const bool wide = N1 > 128;
     G2Kernel k = x3 ? (wide ? pick<MODE_X3, 256>(vec) : pick<MODE_X3, 128>(vec))
                     : (wide ? pick<MODE_F32, 256>(vec) : pick<MODE_F32, 128>(vec));
-    const int64_t blocks = (M + 63) / 64;
+    // whole rounds of 64-row workgroups; what is left as 32-row ones, where these fit
+    // one round
+    const int64_t of64 = (M + 63) / 64, slots = wide ? 512 : 768, rounds = M / 64 / slots * slots;
+    g.tall = (int)(of64 - rounds <= slots / 2 ? rounds : of64);
+    const int64_t blocks = g.tall + (M > 64 * (int64_t)g.tall ? (M - 64 * (int64_t)g.tall + 31) / 32 : 0);
     hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(256), 0, s, g);
     return hipGetLastError() == hipSuccess ? TGEMM_SUCCESS : TGEMM_LAUNCH_FAILED;
 }
