@@ -176,6 +176,11 @@ int run_choice(const Choice& ch, int64_t M, int64_t N, int64_t K, float alpha, c
                                ch.xcd_remap, stream);
         if (rc != TGEMM_NOT_SUPPORTED) return rc;
     }
+    if (ch.joined >= 0) {
+        const int rc = run_gemm(ch.joined, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, ch.group_m, ch.xcd_remap,
+                                stream);
+        if (rc != TGEMM_NOT_SUPPORTED) return rc;
+    }
     const int rc = run_gemm(ch.id, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, ch.group_m, ch.xcd_remap, stream);
     if (ch.unshared < 0 || (rc != TGEMM_CAPTURE_UNPLANNED && rc != TGEMM_ALLOC_FAILED && rc != TGEMM_NOT_SUPPORTED))
         return rc;

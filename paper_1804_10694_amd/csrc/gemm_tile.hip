@@ -44,6 +44,7 @@ hipError_t launch_scale_c(int M, int N, float beta, float* C, int64_t ldc, hipSt
 
 hipError_t launch_gemm(const SchedDesc& d, const GemmArgs& a, hipStream_t s)
 {
+    if (d.inplace) return launch_inplace(d, a, s);
     const unsigned grid = (unsigned)a.tiles_m * (unsigned)a.tiles_n;
     hipLaunchKernelGGL(d.kernel, dim3(grid), dim3(d.threads), 0, s, a);
     return hipGetLastError();

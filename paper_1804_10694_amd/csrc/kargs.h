@@ -32,6 +32,16 @@ struct TileCoord {
     int tm, tn;
 };
 
+// Step 1 of the order below: position of workgroup wg of T.
+__host__ __device__ inline int xcd_order(int wg, int T)
+{
+    const int x = wg % kNumXcd;
+    const int local = wg / kNumXcd;
+    const int base = T / kNumXcd;
+    const int rem = T % kNumXcd;
+    return x * base + (x < rem ? x : rem) + local;
+}
+
 // Tiling map of the Tiramisu paper (the map of a tiling command, Section III-C,
 // as the introduction of Section V writes it: i0 = floor(i/T), i1 = i % T
 // in each dimension): workgroup `wg` owns macro-tile (tm, tn) and computes rows
@@ -46,14 +56,7 @@ __host__ __device__ inline TileCoord map_tile(int wg, int tiles_m, int tiles_n, 
                                               int xcd_remap)
 {
     const int T = tiles_m * tiles_n;
-    int s = wg;
-    if (xcd_remap) {
-        const int x = wg % kNumXcd;
-        const int local = wg / kNumXcd;
-        const int base = T / kNumXcd;
-        const int rem = T % kNumXcd;
-        s = x * base + (x < rem ? x : rem) + local;
-    }
+    const int s = xcd_remap ? xcd_order(wg, T) : wg;
     const int per_group = group_m * tiles_n;
     const int g = s / per_group;
     const int first_m = g * group_m;

@@ -209,8 +209,7 @@ int gemm_f32(int64_t M, int64_t N, int64_t K, const float* A, int64_t lda, const
     Choice c;
     int rc = default_schedule(M, N, K, TGEMM_F32, vec_ok(A, lda, B, ldb, TGEMM_F32), &c);
     if (rc != TGEMM_SUCCESS) return rc;
-    return run_gemm(c.unshared >= 0 ? c.unshared : c.id, M, N, K, 1.f, A, lda, B, ldb, 0.f, C, ldc, c.group_m,
-                    c.xcd_remap, s);
+    return run_gemm(c.id, M, N, K, 1.f, A, lda, B, ldb, 0.f, C, ldc, c.group_m, c.xcd_remap, s);
 }
 
 // ------------------------------------------------------- networks of few tiles

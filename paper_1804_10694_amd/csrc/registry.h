@@ -34,6 +34,7 @@ const SchedDesc* packed_schedules(int* n);  // packed-operand f32, x3, bf16, fp8
 const SchedDesc* inplace_schedules(int* n); // in-place f32 and x3 (gemm_inplace.hip)
 // Whether an in-place schedule reaches every row it loads with 32-bit buffer
 // offsets for these row strides.
+bool inplace_joined(int64_t M, int64_t N);  // f32: 64 x 64 tiles run joined to 128 x 128
 bool inplace_reach_ok(const SchedDesc& d, int64_t lda, int64_t ldb);
 
 // Packed schedules (gemm_packed.hip): index within packed_schedules().
@@ -81,6 +82,7 @@ int packed_index(int id);
 
 // Stream-ordered launches (defined in the HIP translation units).
 hipError_t launch_gemm(const SchedDesc& d, const GemmArgs& a, hipStream_t s);
+hipError_t launch_inplace(const SchedDesc& d, const GemmArgs& a, hipStream_t s);
 hipError_t launch_scale_c(int M, int N, float beta, float* C, int64_t ldc, hipStream_t s);
 hipError_t launch_quantize(int rows, int cols, const float* X, int64_t ldx, void* Q, int64_t ldq,
                            float* S, int dtype, hipStream_t s);

@@ -154,6 +154,7 @@ int direct_schedule(int64_t M, int64_t N, int64_t K, int dtype, bool vec_allowed
     out->group_m = 8;
     out->xcd_remap = 1;
     out->reg = -1;
+    out->joined = -1;
     out->unshared = -1;
     return TGEMM_SUCCESS;
 }
@@ -329,16 +330,13 @@ bool scaled_needs_packing(int64_t M, int64_t N, int64_t K)
 }
 
 // The stream-K form that beats schedule `id`, the table rule's, because it shares
-// the last round of tiles out evenly, or -1.  Set from 60 x3 and 50 f32 shapes of
-// M, N in [800, 8192] and K in [512, 8192], time of the form / of the schedule:
-//  - x3 256 x 256, one tile per CU and round.  A last round of up to 96 tiles:
+// the last round of tiles out evenly, or -1.  Set from 60 x3 shapes of M, N in
+// [1000, 8192] and K in [512, 8192], time of the form / of the schedule:
+//  - 256 x 256 tiles, one per CU and round.  A last round of up to 96 tiles:
 //    0.77 (264 tiles, K 2428) to 0.93 (350, 5348); 372 tiles 1.00, 441 1.05.
 //    Below a round the alternative is 128 x 128 tiles: 0.80 (84 tiles, 5572) to
 //    0.97 (78, 2075) up to 100 tiles, 1.01 to 1.05 from 108.  Shallower K pays the
 //    exchange of sums for too little: 289 tiles 0.97 at K 1024, 112 1.08 at 1530.
-//  - f32 128 x 128, where the fullest CU has an eighth more in-place tiles than the
-//    average: 0.80 (520 tiles for 256 CUs, K 4037) to 0.91 (1134, 5135); at less
-//    0.95 (1155, 2882) to 1.10 (754).  K 794 and 947 1.01 and 1.00.
 static int shared_form(int64_t M, int64_t N, int64_t K, int dtype, int id)
 {
     auto tiles = [&](int b) { return ((M + b - 1) / b) * ((N + b - 1) / b); };
@@ -349,10 +347,6 @@ static int shared_form(int64_t M, int64_t N, int64_t K, int dtype, int id)
         if (d.BM == 256 ? t > 256 && last > 0 && last <= 96 : t >= 64 && t <= 100)
             return find_schedule(dtype, 256, 256, 32, 0, 2, 4, -1, 32, 1);
     }
-    if (dtype == TGEMM_F32 && d.inplace && d.BM == 128 && K >= 1024) {
-        const int64_t t = tiles(128), fullest = (t + 255) / 256;
-        if (t >= 512 && 8 * fullest * 256 >= 9 * t) return find_schedule(dtype, 128, 128, 16, 0, 2, 2, -1, 32, 1);
-    }
     return -1;
 }
 
@@ -361,7 +355,10 @@ int default_schedule(int64_t M, int64_t N, int64_t K, int dtype, bool vec_allowe
     const int rc = table_rule(M, N, K, dtype, vec_allowed, out);
     if (rc != TGEMM_SUCCESS) return rc;
     out->reg = reg_choice(M, N, K, dtype);
+    out->joined = -1;
     out->unshared = -1;
+    if (dtype == TGEMM_F32 && schedule(out->id).inplace && schedule(out->id).BM == 64 && inplace_joined(M, N))
+        out->joined = find_schedule(dtype, 128, 128, 16, 1, 2, 2, -1, 32, 0, 1);
     const int sk = shared_form(M, N, K, dtype, out->id);
     if (sk >= 0) {
         out->unshared = out->id;
@@ -392,6 +389,7 @@ int select_schedule(int64_t M, int64_t N, int64_t K, int dtype, bool vec_allowed
                 out->group_m = 8;
                 out->xcd_remap = 1;
                 out->reg = -1;
+                out->joined = -1;
                 out->unshared = -1;
                 return TGEMM_SUCCESS;
             }

@@ -12,6 +12,8 @@ struct Choice {
     int xcd_remap;
     int reg = -1;  // register tile that runs the problem instead of the schedule where it can
                    // (set by the built-in rule only: the table's ids name LDS-pipeline schedules)
+    int joined = -1;    // 128 x 128 in-place schedule that runs the problem instead of the 64 x 64 one
+                        // named, with the same sums
     int unshared = -1;  // the rule's schedule where the stream-K form it chose finds no workspace
 };
 

@@ -56,11 +56,10 @@ def test_rounds_bit_exact_on_integers(tg, dtype, shape):
             np.testing.assert_array_equal(C.cpu().numpy().astype(np.float64), ref, err_msg=tg.schedule_key(sid))
 
 
-@pytest.mark.parametrize("dtype,shape", [("x3", (4096, 4352, 2000)), ("f32", (6608, 1249, 1100))])
-def test_shared_choice_without_workspace(tg, dtype, shape):
+def test_shared_choice_without_workspace(tg):
     # the rule's stream-K choice, and what runs in its place where it can have no
     # workspace: on a stream first seen under capture, and in the call that allocates nothing
-    M, N, K = shape
+    dtype, (M, N, K) = "x3", (4096, 4352, 2000)
     A, B, C0 = inputs.integer_inputs(M, N, K, seed=71, r=8)
     assert tg.schedule_info(tg.select_schedule(M, N, K, dtype)[0])["split"] == 1
     ref = oracle.gemm(A, B, C0, 1.0, 0.5)

@@ -20,11 +20,7 @@ def tg():
     ("x3", (2560, 2817, 2000), False),     # 120
     ("x3", (1800, 1793, 2000), True),      # 8 x 8 = 64
     ("x3", (1790, 1793, 2000), False),     # 7 x 8 = 56
-    ("f32", (6608, 1249, 4037), True),     # 520 of 128 x 128: 3 on some CUs, 2.03 on average
-    ("f32", (6608, 1249, 1023), False),
-    ("f32", (1644, 7418, 3628), False),    # 754: 2.95 on average
-    ("f32", (6878, 2565, 5135), True),     # 1134: 5 on some, 4.43 on average
-    ("f32", (4096, 4096, 4096), False),    # 1024: 4 everywhere
+    ("f32", (6608, 1249, 4037), False),    # f32 shares the last round as quarters of tiles
 ])
 def test_shared_rule(tg, dtype, shape, shared):
     assert tg.schedule_info(tg.select_schedule(*shape, dtype)[0])["split"] == int(shared)
