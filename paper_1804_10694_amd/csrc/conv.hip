@@ -42,6 +42,7 @@ int ensure_device(hipStream_t stream);
 // NHWC input geometry and the filter size R (odd; padding R / 2, stride 1).
 struct ConvGeom {
     int H, W, C, R;
+    int inner = 0;  // x3 in steps of 16 channels: steps per tap and group of channels (0: a tap's all)
 };
 
 // Tap t of an R x R filter (row-major over dy, dx) as an offset from the output
@@ -198,8 +199,8 @@ struct ConvStepsA {
     static constexpr uint32_t OOB = 0xfffffff0u;  // at or past the end of any X here (below 2^32 - 31 bytes)
 
     __amdgpu_buffer_rsrc_t r;
-    int wave, H, W, C, half, k;      // k: first of the next step, this lane's first unit
-    int taps;                        // taps left from the current one on (0: past K)
+    int wave, H, W, C, half, inner, part;
+    int taps;                        // taps left from the current one on (0: past K); inner: steps
     int ci, dy, dx;                  // channel and tap of k
     uint32_t at[NI];                 // byte offset of (output pixel, channel 0), the unit's array added
     int py[NI], px[NI];              // output pixel's y (far outside past M) and x
@@ -222,7 +223,9 @@ struct ConvStepsA {
         ci = first - tap * C;
         dy = -half + tap / R;
         dx = -half + tap % R;
-        taps = R * R - tap;
+        inner = g.inner;
+        part = 0;
+        taps = inner ? R * R * (C / 16) : R * R - tap;
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
             const int m = m0 + (wave * NI + i) * (64 / SP::UK) + lane / SP::UK;
@@ -243,6 +246,19 @@ struct ConvStepsA {
             __builtin_amdgcn_raw_ptr_buffer_load_lds(
                 r, (__attribute__((address_space(3))) void*)(stage + (wave * NI + i) * 1024), 16,
                 (int)(in ? at[i] + off : OOB), 0, 0, 0);
+        }
+        if (inner) {
+            --taps;
+            ci += 16;
+            if (++part < inner) return;
+            part = 0;
+            const bool line = ++dx > half;
+            dx = line ? -half : dx;
+            dy += line;
+            const bool all = dy > half;
+            dy = all ? -half : dy;
+            ci -= all ? 0 : 16 * inner;
+            return;
         }
         ci += 16;
 #pragma unroll
@@ -269,6 +285,30 @@ __global__ void __launch_bounds__(256) conv_split_kernel(const float* X, char* o
         split_bf16x8(x, h, l);
         *reinterpret_cast<bf16x8*>(out + 32 * i) = h;
         *reinterpret_cast<bf16x8*>(out + 32 * i + 16) = l;
+    }
+}
+
+// The filter in steps of 16 channels of one tap, taps inside (ConvGeom::inner): step
+// s of column n is part s % inner of (channel group) * taps + tap = s / inner, in units as
+// StepPack has them.  A block has 256 columns of one step.
+__global__ void __launch_bounds__(256) conv_filter_kernel(const float* Wt, int C, int N, int taps, int inner, char* P,
+                                                         int Kp, int Np)
+{
+    using SP = StepPack<MODE_X3>;
+    const int blocks = Np / 256, s = blockIdx.x / blocks, n = (blockIdx.x - s * blocks) * 256 + threadIdx.x;
+    const int group = s / (taps * inner), rest = s - group * taps * inner;
+    const int tap = rest / inner, c0 = group * inner + rest - tap * inner;
+    char* dst = P + ((int64_t)(n / SP::ROWS) * (Kp / SP::HK) + s) * SP::CHUNK;
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+        float x[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            x[e] = n < N ? Wt[((int64_t)tap * C + 16 * c0 + 8 * g + e) * N + n] : 0.f;
+        bf16x8 h, l;
+        split_bf16x8(x, h, l);
+        *reinterpret_cast<bf16x8*>(dst + pk_slot<SP::UK>(n % SP::ROWS, g) * 16) = h;
+        *reinterpret_cast<bf16x8*>(dst + pk_slot<SP::UK>(n % SP::ROWS, 2 + g) * 16) = l;
     }
 }
 
@@ -421,9 +461,22 @@ int conv_packed_run(const ConvPacked& p, int64_t M, int64_t Cin, int64_t Cout, i
     char* Blo = x3 ? Bp + Np * Kp * es : nullptr;
     char* Ah = x3 ? Bp + wbytes : nullptr;
     char* Al = x3 ? Ah + M * Cin * es : nullptr;
+    ConvGeom geom = g;
     if (p.turns) {
-        rc = launch_step_cols(p.mode, Wt, Cout, K, Cout, Bp, Np, Kp, s);
-        if (rc != TGEMM_SUCCESS) return rc;
+        // k in the order (64, 32 or 16 channels, tap, channel): a tile's nine reads of a pixel
+        // come within a few steps, while its line is in the XCD's L2; tap by tap over all
+        // channels they are C / 16 steps apart (8 MB of X per XCD at 256) and come from the
+        // Infinity Cache, whose 28 bytes/ns per CU are about what the matrix cores ask of X.
+        // 3 x 3, 32 x 56 x 56 x 256 -> 256 377 us -> 359, 16 x 112 x 112 x 128 -> 256 385 -> 367,
+        // 32 x 28 x 28 x 512 -> 1024 612 -> 583; 16 channels at a time 366, 372, 591.
+        geom.inner = Cin % 64 == 0 ? 4 : Cin % 32 == 0 ? 2 : Cin % 16 == 0 ? 1 : 0;
+        if (geom.inner) {
+            hipLaunchKernelGGL(conv_filter_kernel, dim3((unsigned)(Np / 256 * (K / 16))), dim3(256), 0, s, Wt,
+                               (int)Cin, (int)Cout, g.R * g.R, geom.inner, Bp, (int)Kp, (int)Np);
+        } else {
+            rc = launch_step_cols(p.mode, Wt, Cout, K, Cout, Bp, Np, Kp, s);
+            if (rc != TGEMM_SUCCESS) return rc;
+        }
         const int64_t groups = M * Cin / 8;
         hipLaunchKernelGGL(conv_split_kernel, dim3((unsigned)std::min<int64_t>((groups + 255) / 256, 65536)), dim3(256),
                            0, s, X, Ah, groups);
@@ -453,7 +506,7 @@ int conv_packed_run(const ConvPacked& p, int64_t M, int64_t Cin, int64_t Cout, i
     a.xcd_remap = 1;
     if ((int64_t)a.tiles_m * a.tiles_n > INT32_MAX) return TGEMM_NOT_SUPPORTED;
     hipLaunchKernelGGL(p.kernel[variant(g, runtime_r)], dim3((unsigned)(a.tiles_m * a.tiles_n)),
-                       dim3(p.threads), 0, s, a, g);
+                       dim3(p.threads), 0, s, a, geom);
     return hipGetLastError() == hipSuccess ? TGEMM_SUCCESS : TGEMM_LAUNCH_FAILED;
 }
 

@@ -1,0 +1,32 @@
+"""x3 convolution on 256 x 256 tiles: channel groups of 64, 32, 16 and none, taps inside.
+
+Bit-exact on small integers against the FP64 convolution oracle (bars as in
+test_gpu_conv.py), for channel counts of each group size with one and several groups,
+filters of one tap and more, images smaller than the filter, and columns around one tile.
+"""
+import numpy as np
+import pytest
+import torch
+
+from oracle import conv as OC
+
+pytestmark = pytest.mark.gpu
+DEV = torch.device("cuda:0")
+
+
+@pytest.mark.parametrize("cin", [8, 16, 24, 32, 48, 64, 96, 192])
+@pytest.mark.parametrize("R,image,cout", [(1, (2, 9, 15), 5), (3, (3, 11, 13), 257), (5, (5, 2, 3), 256),
+                                          (7, (1, 20, 17), 30)])
+def test_channel_groups(cin, R, image, cout):
+    from paper_1804_10694_amd import tgemm as tg
+    print(f"conv order cin={cin} R={R} {image} cout={cout}", flush=True)
+    g = torch.Generator().manual_seed(cin + R)
+    X = torch.randint(-4, 5, (*image, cin), generator=g).float()
+    Wt = torch.randint(-4, 5, (R, R, cin, cout), generator=g).float()
+    Y0 = torch.randint(-4, 5, (*image, cout), generator=g).float()
+    ref = OC.conv2d(X, Wt, Y0, 1.5, 0.5)
+    for runtime_r in (False, True):
+        Y = Y0.to(DEV)
+        tg.conv2d(X.to(DEV), Wt.to(DEV), Y, 1.5, 0.5, "x3", path="packed", shape=1, runtime_r=runtime_r)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(Y.cpu().numpy().astype(np.float64), ref.reshape(Y.shape))
