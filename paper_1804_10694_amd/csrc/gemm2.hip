@@ -51,7 +51,7 @@ struct G2Args {
 
 template <int MODE, int N1P, int RB>
 struct G2Cfg {
-    static constexpr int BK = 32, NT = 256, AHEAD = 3;
+    static constexpr int BK = 32, AHEAD = 3;
     using P1 = ICfg<MODE, RB, N1P, BK, 1, 4, 2>;  // phase 1: an RB x N1P block of T, 4 waves side by side
     template <int TN>
     using P2 = ICfg<MODE, RB, 128 * TN, BK, 1, 4, 2>;  // phase 2: an RB x 128 TN chunk of E

@@ -25,8 +25,9 @@ import csv
 import json
 from collections import OrderedDict, defaultdict
 
-MAIN_KERNELS = ("gemm_kernel", "packed_kernel", "packed_sk_kernel", "scaled_kernel", "inplace_gemm_kernel")
-PACK_KERNELS = ("pack_rows_kernel", "pack_cols_kernel")
+MAIN_KERNELS = ("gemm_kernel", "packed_kernel", "packed_sk_kernel", "scaled_kernel", "inplace_gemm_kernel",
+                "inplace_rest_kernel")
+PACK_KERNELS = ("pack_rows_kernel", "pack_cols_kernel", "step_rows_kernel", "step_cols_kernel")
 COPY_KERNEL = "__amd_rocclr_copyBuffer"
 
 
@@ -109,6 +110,12 @@ def match(calls, bench):
         if "packed_sk_kernel" in main["name"]:
             tile = lambda p: ",%d,%d," % tuple(int(x) for x in p["schedule_key"].split(":")[2].split("x")[:2])
             cands = [c for c in grids.get("sk", []) if tile(c[2]) in short_name(main["name"])]
+        elif "inplace_rest_kernel" in main["name"]:
+            # f32 128 x 128 tiles and quarters of them, whichever in-place schedule is named
+            for label in (lb for lb, _, p in sum(grids.values(), []) if p.get("inplace") and lb.startswith("f32")):
+                got[label].append((main, packs))
+                break
+            continue
         else:
             cands = grids.get(main["grid"], [])
         # paths sharing a grid are told apart by the main kernel's mode (template argument 0/1)
