@@ -133,53 +133,87 @@ struct ConvRowsA {
     static constexpr int LOADS = CF::NARR * NI;  // loads per wave per panel
     static constexpr int OOB = INT32_MIN;  // offset 2^31: beyond any resource here, reads zero
 
-    __amdgpu_buffer_rsrc_t r, rl;
-    int wave, K, H, W, C;
-    ConvGeom g;
-    int ku[NI];                   // first k of this lane's unit within a panel
-    int pix[NI], py[NI], px[NI];  // output pixel of this lane's row (-1 past M), its y and x
+    // Instructions DS apart load the same unit of their rows (the swizzle of pk_slot
+    // repeats), so there are DS positions in k.  Panels are issued in order, so a tap
+    // and channel advance by addition: beside waves that keep the matrix core busy each
+    // instruction of a division takes about an MFMA's time.  With two divisions per load
+    // and panel, 3 x 3 layers f32 32 x 56 x 56 x 256 -> 256 1045 us, now 1000; 32 x 28 x 28
+    // x 128 -> 128 109 -> 98; x3 there 58.7 -> 50.9, 8 x 14 x 14 x 512 -> 512 148 -> 127.
+    static constexpr int DS = UK <= 4 ? 1 : UK / 4 < NI ? UK / 4 : NI;
 
-    __device__ __forceinline__ void init(const PackedArgs& a, int m0, int lane, int wave_, const Geom& geom)
+    __amdgpu_buffer_rsrc_t r, rl;
+    int wave, K, H, W, C, R;
+    int k[DS], ci[DS], dy[DS], dx[DS];  // next panel's k, its channel and tap
+    uint32_t at[NI];                    // byte of this lane's output pixel
+    int py[NI], px[NI];                 // its y (far outside past M) and x
+
+    __device__ __forceinline__ void place(int d)
+    {
+        const int tap = k[d] / C;
+        ci[d] = k[d] - tap * C;
+        const int q = tap / R;
+        dy[d] = q - R / 2;
+        dx[d] = tap - q * R - R / 2;
+    }
+
+    __device__ __forceinline__ void init(const PackedArgs& a, int m0, int lane, int wave_, const Geom& g)
     {
         wave = wave_;
-        g = geom;
         K = a.K;
         H = g.H;
         W = g.W;
         C = g.C;
+        R = FR > 0 ? FR : g.R;
         const int bytes = a.M * C * CF::ES;  // below 2^31 (checked on the host)
         r = make_rsrc(a.A, bytes);
         rl = CF::MODE == MODE_X3 ? make_rsrc(a.Alo, bytes) : r;
 #pragma unroll
+        for (int d = 0; d < DS; ++d) {
+            k[d] = (((lane % UK) ^ (4 * (wave * NI + d) + lane / 16)) & (UK - 1)) * KU;
+            place(d);
+        }
+#pragma unroll
         for (int i = 0; i < NI; ++i) {
-            const int ig = wave * NI + i;
-            ku[i] = (((lane % UK) ^ (4 * ig + lane / 16)) & (UK - 1)) * KU;
-            const int m = m0 + ig * (64 / UK) + lane / UK;
+            const int m = m0 + (wave * NI + i) * (64 / UK) + lane / UK;
             const int row = m / W;
-            pix[i] = m < a.M ? m : -1;
             px[i] = m - row * W;
-            py[i] = row % H;
+            py[i] = m < a.M ? row % H : INT32_MIN / 2;
+            at[i] = (uint32_t)m * (uint32_t)(C * CF::ES);
         }
     }
 
-    __device__ __forceinline__ void issue(int panel, char* stage) const
+    __device__ __forceinline__ void issue(int, char* stage)
     {
+        uint32_t off[DS];
+#pragma unroll
+        for (int d = 0; d < DS; ++d) off[d] = ((uint32_t)(dy[d] * W + dx[d]) * (uint32_t)C + ci[d]) * CF::ES;
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
-            const int ig = wave * NI + i;
-            const int k = panel * CF::BK + ku[i];
-            const int tap = k / C, ci = k - tap * C;
-            int dy, dx;
-            tap_offset<FR>(tap, g, dy, dx);
-            const int iy = py[i] + dy, ix = px[i] + dx;
-            const bool in = pix[i] >= 0 && k < K && iy >= 0 && iy < H && ix >= 0 && ix < W;
-            const int voff = in ? ((pix[i] + dy * W + dx) * C + ci) * CF::ES : OOB;
+            const int ig = wave * NI + i, d = i % DS;
+            const bool in = k[d] < K && (unsigned)(py[i] + dy[d]) < (unsigned)H &&
+                            (unsigned)(px[i] + dx[d]) < (unsigned)W;
+            const int voff = in ? (int)(at[i] + off[d]) : OOB;
             auto* dst = (__attribute__((address_space(3))) void*)(stage + ig * 64 * 16);
             __builtin_amdgcn_raw_ptr_buffer_load_lds(r, dst, 16, voff, 0, 0, 0);
             if (CF::MODE == MODE_X3) {
                 auto* dlo = (__attribute__((address_space(3))) void*)(stage + CF::LDS_A + ig * 64 * 16);
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(rl, dlo, 16, voff, 0, 0, 0);
             }
+        }
+#pragma unroll
+        for (int d = 0; d < DS; ++d) {
+            k[d] += CF::BK;
+            if (C < CF::BK) {  // a panel is more than one tap further
+                place(d);
+                continue;
+            }
+            ci[d] += CF::BK;
+            const bool wrap = ci[d] >= C;
+            ci[d] -= wrap ? C : 0;
+            dx[d] += wrap;
+            const bool line = dx[d] > R / 2;
+            dy[d] += line;
+            dx[d] -= line ? R : 0;
         }
     }
 };
