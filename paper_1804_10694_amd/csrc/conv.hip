@@ -397,6 +397,15 @@ const ConvPacked kConvPacked[] = {
     TG_CONVP(TGEMM_F32_BF16X3, MODE_X3, 128, 128, 16, 2, 2, 2),
 };
 
+// f32 layers of fewer than 128 tiles of 128 x 128 leave half of the CUs idle in the
+// packed kernel: the direct one on 64 x 64 tiles takes 0.52 to 0.77 of its time there (52
+// tiles, 8 x 14 x 14 x 512 -> 512, 351 us / 197; 98, 8 x 28 x 28 x 256 -> 256, 179 / 136), 1.23
+// at 196.  x3 gains less than the 8% it loses elsewhere (126 / 136, 71 / 67).
+bool conv_few_tiles(int dtype, int64_t M, int64_t Cout)
+{
+    return dtype == TGEMM_F32 && Cout % 4 == 0 && ((M + 127) / 128) * ((Cout + 127) / 128) < 128;
+}
+
 int conv_default_shape(int dtype, int64_t M, int64_t Cout)
 {
     if (dtype != TGEMM_F32_BF16X3) return 0;
@@ -581,7 +590,8 @@ int conv_run(int64_t batch, int64_t H, int64_t W, int64_t Cin, int64_t Cout, int
     const ConvGeom g{(int)H, (int)W, (int)Cin, (int)R};
     const bool packed_ok = conv_packed_ok(M, Cin, K, dtype);
     if (packed && !packed_ok) return TGEMM_NOT_SUPPORTED;
-    if (path == TGEMM_CONV_AUTO && packed_ok) packed = conv_packed(dtype, conv_default_shape(dtype, M, Cout));
+    if (path == TGEMM_CONV_AUTO && packed_ok && !conv_few_tiles(dtype, M, Cout))
+        packed = conv_packed(dtype, conv_default_shape(dtype, M, Cout));
     if (packed) {
         rc = conv_packed_run(*packed, M, Cin, Cout, K, alpha, X, Wt, beta, Y, g, runtime_r, s);
         // under capture with no workspace yet: the direct kernel needs none

@@ -53,3 +53,17 @@ def test_panel_steps(dtype, cin, R):
         tg.conv2d(X.to(DEV), Wt.to(DEV), Y, 1.5, 0.5, dtype, path="packed", shape=shape)
         torch.cuda.synchronize()
         np.testing.assert_array_equal(Y.cpu().numpy().astype(np.float64), ref.reshape(Y.shape))
+
+
+@pytest.mark.parametrize("image,cout", [((4, 45, 45), 256), ((4, 44, 45), 256), ((4, 45, 45), 255), ((1, 3, 5), 4)])
+def test_auto_around_128_tiles(image, cout):
+    from paper_1804_10694_amd import tgemm as tg
+    g = torch.Generator().manual_seed(sum(image) + cout)
+    X = torch.randint(-4, 5, (*image, 8), generator=g).float()
+    Wt = torch.randint(-4, 5, (3, 3, 8, cout), generator=g).float()
+    Y0 = torch.randint(-4, 5, (*image, cout), generator=g).float()
+    print(f"conv auto {image} cout={cout}", flush=True)
+    Y = Y0.to(DEV)
+    tg.conv3x3(X.to(DEV), Wt.to(DEV), Y, 1.5, 0.5, "f32")
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(Y.cpu().numpy().astype(np.float64), OC.conv2d(X, Wt, Y0, 1.5, 0.5).reshape(Y.shape))
