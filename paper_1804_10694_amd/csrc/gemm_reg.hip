@@ -39,10 +39,11 @@ struct RegTiles {
 template <class CF>
 int launch(RegArgs a, hipStream_t s)
 {
-    a.tiles_m = (a.M + CF::BM - 1) / CF::BM;
-    a.tiles_n = (a.N + CF::BN - 1) / CF::BN;
-    const int64_t tiles = (int64_t)a.tiles_m * a.tiles_n * a.batch;
-    if (tiles > INT32_MAX) return TGEMM_NOT_SUPPORTED;
+    a.tiles_m = (int)(((int64_t)a.M + CF::BM - 1) / CF::BM);
+    a.tiles_n = (int)(((int64_t)a.N + CF::BN - 1) / CF::BN);
+    const int64_t per = (int64_t)a.tiles_m * a.tiles_n;
+    if (per > INT32_MAX || !grid_fits(per * a.batch, CF::NT)) return TGEMM_NOT_SUPPORTED;
+    const int64_t tiles = per * a.batch;
     hipLaunchKernelGGL(reg_gemm_kernel<CF>, dim3((unsigned)tiles), dim3(CF::NT), 0, s, a);
     return hipGetLastError() == hipSuccess ? TGEMM_SUCCESS : TGEMM_LAUNCH_FAILED;
 }

@@ -80,6 +80,12 @@ constexpr int64_t packed_kp(int64_t K, int64_t es)
 // Position of a schedule id inside packed_schedules(), or -1.
 int packed_index(int id);
 
+// Whether a launch of this many workgroups can be made.  A grid dimension counts
+// threads in 32 bits, and a launch beyond that returns success and runs the
+// remainder modulo 2^32 only.
+constexpr bool grid_fits(int64_t blocks, int threads) { return blocks <= (int64_t)UINT32_MAX / threads; }
+static_assert(grid_fits((1 << 24) - 1, 256) && !grid_fits(1 << 24, 256), "2^24 workgroups of 256 threads are too many");
+
 // Stream-ordered launches (defined in the HIP translation units).
 hipError_t launch_gemm(const SchedDesc& d, const GemmArgs& a, hipStream_t s);
 hipError_t launch_inplace(const SchedDesc& d, const GemmArgs& a, hipStream_t s);

@@ -1,0 +1,29 @@
+"""Calls whose tiles would need a grid of 2^32 threads or more, which the runtime truncates
+without an error.  Small integers: every result is exact."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+DEV = torch.device("cuda:0")
+
+
+@pytest.fixture(scope="module")
+def tg():
+    from paper_1804_10694_amd import tgemm
+    tgemm.set_policy("default")
+    yield tgemm
+    torch.cuda.empty_cache()
+
+
+def _ints(*shape):
+    return torch.randint(-4, 5, shape, device=DEV, dtype=torch.int8).float()
+
+
+@pytest.mark.parametrize("P", [16383, 16385])  # 1024 tiles of 32 rows a product: just below and above 2^24
+def test_reordered_contraction_of_many_tiles(tg, P):
+    M = 1024 * 32 - 31
+    A, B = _ints(1, M, P), _ints(P, 1, 1)
+    C = torch.full((P, M, 1), float("nan"), device=DEV)
+    tg.contract(A, [1, 0, 9], B, [9, 2, 1], C, [9, 0, 2])
+    torch.cuda.synchronize()
+    assert torch.equal(C[:, :, 0], A[0].T * B[:, 0])
