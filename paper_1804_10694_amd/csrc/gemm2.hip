@@ -28,6 +28,8 @@
 // 8192 x 1024 x 256 x 1024 f32 158 -> 83; 1000 rows 42 -> 24.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "../../include/tgemm.h"
 #include "kargs.h"
 #include "registry.h"
@@ -308,15 +310,12 @@ extern "C" int tgemm_gemm2(int64_t M, int64_t N1, int64_t N2, int64_t K, float a
     auto al16 = [](const void* p, int64_t ld) { return reinterpret_cast<uintptr_t>(p) % 16 == 0 && ld % 4 == 0; };
     const bool vec = al16(A, lda) && al16(B, ldb) && al16(D, ldd) && K % 4 == 0 && N1 % 4 == 0 && N2 % 4 == 0;
     G2Args g;
-    g.A = reinterpret_cast<const char*>(A);
     g.B = reinterpret_cast<const char*>(B);
     g.D = reinterpret_cast<const char*>(D);
-    g.E = E;
     g.lda = lda;
     g.ldb = ldb;
     g.ldd = ldd;
     g.lde = lde;
-    g.M = (int)M;
     g.N1 = (int)N1;
     g.N2 = (int)N2;
     g.K = (int)K;
@@ -328,10 +327,18 @@ extern "C" int tgemm_gemm2(int64_t M, int64_t N1, int64_t N2, int64_t K, float a
     G2Kernel k = x3 ? (wide ? pick<MODE_X3, 256>(vec) : pick<MODE_X3, 128>(vec))
                     : (wide ? pick<MODE_F32, 256>(vec) : pick<MODE_F32, 128>(vec));
     // whole rounds of 64-row workgroups; what is left as 32-row ones, where these fit
-    // one round
-    const int64_t of64 = (M + 63) / 64, slots = wide ? 512 : 768, rounds = M / 64 / slots * slots;
-    g.tall = (int)(of64 - rounds <= slots / 2 ? rounds : of64);
-    const int64_t blocks = g.tall + (M > 64 * (int64_t)g.tall ? (M - 64 * (int64_t)g.tall + 31) / 32 : 0);
-    hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(256), 0, s, g);
+    // one round.  A launch takes at most 2^29 rows: a grid counts threads in 32 bits.
+    constexpr int64_t kRows = int64_t(1) << 29;
+    static_assert(grid_fits(kRows / 64 + 768, 256), "the workgroups of a launch, 32-row ones among them");
+    const int64_t slots = wide ? 512 : 768;
+    for (int64_t m = 0; m < M; m += kRows) {
+        const int64_t rows = std::min(M - m, kRows), of64 = (rows + 63) / 64, rounds = rows / 64 / slots * slots;
+        g.A = reinterpret_cast<const char*>(A + m * lda);
+        g.E = E + m * lde;
+        g.M = (int)rows;
+        g.tall = (int)(of64 - rounds <= slots / 2 ? rounds : of64);
+        const int64_t low = rows - 64 * (int64_t)g.tall, blocks = g.tall + (low > 0 ? (low + 31) / 32 : 0);
+        hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(256), 0, s, g);
+    }
     return hipGetLastError() == hipSuccess ? TGEMM_SUCCESS : TGEMM_LAUNCH_FAILED;
 }

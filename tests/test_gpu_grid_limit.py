@@ -27,3 +27,13 @@ def test_reordered_contraction_of_many_tiles(tg, P):
     tg.contract(A, [1, 0, 9], B, [9, 2, 1], C, [9, 0, 2])
     torch.cuda.synchronize()
     assert torch.equal(C[:, :, 0], A[0].T * B[:, 0])
+
+
+@pytest.mark.parametrize("M", [2 ** 30 - 64, 2 ** 30 + 2 ** 29 + 33])  # rows past whole rounds of workgroups; three launches
+def test_back_to_back_rows(tg, M):
+    A = _ints(M, 1)
+    B, D = torch.full((1, 1), 2.0, device=DEV), torch.full((1, 1), 3.0, device=DEV)
+    E = torch.full((M, 1), float("nan"), device=DEV)
+    tg.gemm2(A, B, D, E)
+    torch.cuda.synchronize()
+    assert torch.equal(E, A.mul_(6.0))
