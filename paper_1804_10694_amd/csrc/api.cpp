@@ -131,7 +131,7 @@ int run_scaled(int64_t M, int64_t N, int64_t K, float alpha, const void* A, int6
     a.lds_a = (K + 127) / 128;
     a.lds_b = (N + 127) / 128;
     (void)dtype;
-    if ((int64_t)a.tiles_m * a.tiles_n > INT32_MAX) return TGEMM_NOT_SUPPORTED;
+    if (!grid_fits((int64_t)a.tiles_m * a.tiles_n, d.threads)) return TGEMM_NOT_SUPPORTED;
     return launch_gemm(d, a, s) == hipSuccess ? TGEMM_SUCCESS : TGEMM_LAUNCH_FAILED;
 }
 
@@ -152,7 +152,7 @@ int run_gemm(int id, int64_t M, int64_t N, int64_t K, float alpha, const void* A
     const SchedDesc& d = schedule(id);
     if (d.inplace && !inplace_reach_ok(d, lda, ldb)) return TGEMM_NOT_SUPPORTED;
     GemmArgs a = make_args(d, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, group_m, xcd_remap);
-    if ((int64_t)a.tiles_m * a.tiles_n > INT32_MAX) return TGEMM_NOT_SUPPORTED;
+    if (!grid_fits((int64_t)a.tiles_m * a.tiles_n, d.threads)) return TGEMM_NOT_SUPPORTED;
     return launch_gemm(d, a, stream) == hipSuccess ? TGEMM_SUCCESS : TGEMM_LAUNCH_FAILED;
 }
 
@@ -298,7 +298,7 @@ int tgemm_quantize_tiles(int64_t rows, int64_t cols, const float* X, int64_t ldx
     if (rows == 0 || cols == 0) return TGEMM_SUCCESS;
     if (!X || !Q || !S) return TGEMM_INVALID_VALUE;
     const int64_t tiles = ((rows + 127) / 128) * ((cols + 127) / 128);
-    if (tiles > INT32_MAX) return TGEMM_INVALID_VALUE;
+    if (!grid_fits(tiles, 256)) return TGEMM_INVALID_VALUE;
     hipStream_t s = static_cast<hipStream_t>(stream);
     int rc = ensure_device(s);
     if (rc != TGEMM_SUCCESS) return rc;

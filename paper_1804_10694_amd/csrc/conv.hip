@@ -474,7 +474,7 @@ int conv_direct(int64_t M, int64_t Cout, int64_t K, float alpha, const float* X,
     a.tiles_n = (int)((Cout + pick->BN - 1) / pick->BN);
     a.group_m = 8;
     a.xcd_remap = 1;
-    if ((int64_t)a.tiles_m * a.tiles_n > INT32_MAX) return TGEMM_NOT_SUPPORTED;
+    if (!grid_fits((int64_t)a.tiles_m * a.tiles_n, pick->threads)) return TGEMM_NOT_SUPPORTED;
     hipLaunchKernelGGL(pick->kernel[variant(g, runtime_r)], dim3((unsigned)(a.tiles_m * a.tiles_n)),
                        dim3(pick->threads), 0, s, a, g);
     return hipGetLastError() == hipSuccess ? TGEMM_SUCCESS : TGEMM_LAUNCH_FAILED;
@@ -547,7 +547,7 @@ int conv_packed_run(const ConvPacked& p, int64_t M, int64_t Cin, int64_t Cout, i
     a.tiles_n = (int)((Cout + p.BN - 1) / p.BN);
     a.group_m = 8;
     a.xcd_remap = 1;
-    if ((int64_t)a.tiles_m * a.tiles_n > INT32_MAX) return TGEMM_NOT_SUPPORTED;
+    if (!grid_fits((int64_t)a.tiles_m * a.tiles_n, p.threads)) return TGEMM_NOT_SUPPORTED;
     hipLaunchKernelGGL(p.kernel[variant(g, runtime_r)], dim3((unsigned)(a.tiles_m * a.tiles_n)),
                        dim3(p.threads), 0, s, a, geom);
     return hipGetLastError() == hipSuccess ? TGEMM_SUCCESS : TGEMM_LAUNCH_FAILED;

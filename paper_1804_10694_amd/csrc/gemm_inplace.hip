@@ -110,7 +110,7 @@ hipError_t launch_inplace(const SchedDesc& d, const GemmArgs& a, hipStream_t s)
 {
     const int tiles = a.tiles_m * a.tiles_n;
     const int rest = d.dtype == TGEMM_F32 && d.BM == 128 && tiles > 256 ? tiles % 256 : 0;
-    if (rest == 0 || rest > kRestTiles) {
+    if (rest == 0 || rest > kRestTiles || !grid_fits(tiles + 3 * rest, d.threads)) {
         hipLaunchKernelGGL(d.kernel, dim3((unsigned)tiles), dim3(d.threads), 0, s, a);
     } else {
         const dim3 grid((unsigned)(tiles + 3 * rest));

@@ -619,7 +619,7 @@ int launch_step_pack(const void* A, int64_t lda, int64_t M, char* Ap, int64_t Mp
     using SP = StepPack<MODE>;
     constexpr int es = src_bytes<MODE>();
     const int64_t blocks = Mp / SP::ROWS * (Kp / (2 * SP::HK)) * SP::GROUPS;
-    if (blocks > INT32_MAX) return TGEMM_NOT_SUPPORTED;
+    if (!grid_fits(blocks, 256)) return TGEMM_NOT_SUPPORTED;
     const uintptr_t pa = reinterpret_cast<uintptr_t>(A);
     const int vec_a = es == 4 || (pa % 16 == 0 && lda * es % 16 == 0);
     hipLaunchKernelGGL(step_rows_kernel<MODE>, dim3((unsigned)blocks), dim3(256), 0, s, A, lda, (int)M, (int)K, Ap,
@@ -702,7 +702,7 @@ int run_packed_ws(int pid, int64_t M, int64_t N, int64_t K, float alpha, const v
     a.tiles_n = (int)((N + p.BN - 1) / p.BN);
     a.group_m = group_m < 1 ? 1 : group_m;
     a.xcd_remap = xcd_remap ? 1 : 0;
-    if ((int64_t)a.tiles_m * a.tiles_n > INT32_MAX) return TGEMM_NOT_SUPPORTED;
+    if (!grid_fits((int64_t)a.tiles_m * a.tiles_n, p.threads)) return TGEMM_NOT_SUPPORTED;
     const int tiles = a.tiles_m * a.tiles_n;
     if (sk) {
         SkArgs k;

@@ -37,3 +37,14 @@ def test_back_to_back_rows(tg, M):
     tg.gemm2(A, B, D, E)
     torch.cuda.synchronize()
     assert torch.equal(E, A.mul_(6.0))
+
+
+def test_tiles_past_the_limit_are_refused(tg):
+    # 2^24 tiles of 64 x 64 (rows that 16-byte loads cannot take), and of 128 x 128
+    M = 2 ** 30
+    A, B, C = torch.ones(M, 1, device=DEV), torch.ones(1, 1, device=DEV), torch.zeros(M, 1, device=DEV)
+    assert tg.gemm_raw(M, 1, 1, 1.0, A.data_ptr(), 1, B.data_ptr(), 1, 0.0, C.data_ptr(), 1, "f32") == tg.NOT_SUPPORTED
+    X = torch.ones(2 ** 31 - 1, 1, device=DEV)
+    with pytest.raises(tg.TgemmError) as e:
+        tg.quantize_tiles(X, "fp8")
+    assert e.value.status == tg.INVALID_VALUE
