@@ -7,6 +7,13 @@
 
 namespace tg {
 
+// Whether the H rows from r0 on lie within M.  r0 + H may pass 2^31 for a block
+// that starts below M.
+__host__ __device__ constexpr bool block_within(int r0, int H, int M) { return r0 <= M - H; }
+static_assert(block_within(INT32_MAX - 32, 32, INT32_MAX) && !block_within(INT32_MAX - 31, 32, INT32_MAX) &&
+                  !block_within(0, 32, 31) && block_within(0, 32, 32),
+              "whole blocks");
+
 // Writes the TM x TN blocks of AR results a lane holds.  val(i, j, v) puts the
 // AR values of block (i, j) (alpha applied) into v.  Block (i, j) starts at
 // row r0, column c0 of C as origin(i, j, r0, c0) sets them (the same in every
@@ -76,7 +83,7 @@ __device__ __forceinline__ void write_c(float* C, int64_t ldc, int M, int N, flo
             const int64_t left = (int64_t)(M - 1 - r0) * ldc + (N - c0);
             bytes[q] = r0 >= M || left <= 0 ? 0 : left * 4;
             base[q] = C + (int64_t)r0 * ldc + c0;
-            whole = whole && r0 + H <= M;
+            whole = whole && block_within(r0, H, M);
             lo[q] = (c0 + lane_col < N) ? lane_row * ldc4 + lane_col * 4 : (int)0x80000000u;
             val(i, j, v[q]);
         }
