@@ -673,9 +673,8 @@ int run_packed_ws(int pid, int64_t M, int64_t N, int64_t K, float alpha, const v
 
     int rc;
     if (p.step) {
-        rc = p.mode == MODE_FP8    ? launch_step_pack<MODE_FP8>(A, lda, M, Ap, Mp, B, ldb, N, Bp, Np, K, Kp, s)
-             : p.mode == MODE_BF16 ? launch_step_pack<MODE_BF16>(A, lda, M, Ap, Mp, B, ldb, N, Bp, Np, K, Kp, s)
-                                   : launch_step_pack<MODE_X3>(A, lda, M, Ap, Mp, B, ldb, N, Bp, Np, K, Kp, s);
+        rc = p.mode == MODE_FP8 ? launch_step_pack<MODE_FP8>(A, lda, M, Ap, Mp, B, ldb, N, Bp, Np, K, Kp, s)
+                                : launch_step_pack<MODE_X3>(A, lda, M, Ap, Mp, B, ldb, N, Bp, Np, K, Kp, s);
     } else {
         rc = launch_pack_rows(p.mode, A, lda, M, K, Ap, Alo, Mp, Kp, s);
         if (rc == TGEMM_SUCCESS) rc = launch_pack_cols(p.mode, B, ldb, K, N, Bp, Blo, Np, Kp, s);

@@ -282,13 +282,13 @@ struct PCfg {
 // ("steps": four 16-byte units per row), NS of them in a ring, operands packed
 // in step order (StepPack).
 template <int MODE_, int BM_, int BN_, int WGM_, int WGN_, int NS_, int MS_ = 32>
-struct TCfg : PCfg<MODE_, BM_, BN_, MODE_ == MODE_FP8 ? 64 : MODE_ == MODE_BF16 ? 32 : 16, WGM_, WGN_, NS_, MS_> {
+struct TCfg : PCfg<MODE_, BM_, BN_, MODE_ == MODE_FP8 ? 64 : 16, WGM_, WGN_, NS_, MS_> {
     static constexpr bool TURNS = true;
-    static_assert(WGM_ * WGN_ == 8 && MODE_ != MODE_F32, "two waves per SIMD, bf16 or e4m3 matrix cores");
+    static_assert(WGM_ * WGN_ == 8 && (MODE_ == MODE_X3 || MODE_ == MODE_FP8), "two waves per SIMD, x3 or e4m3");
 };
 
-// Step-packed operands.  A step holds four units of a row: 32 k (bf16), 64 k
-// (e4m3), or 16 k as two units of high and two of low parts (x3).  256 rows by
+// Step-packed operands.  A step holds four units of a row: 64 k (e4m3), or
+// 16 k as two units of high and two of low parts (x3).  256 rows by
 // one step form a chunk of 16 KB in the very order LDS holds it (pk_slot), and
 // the chunks of a tile follow each other along k, so a workgroup streams its
 // operand front to back and every load instruction moves one run of 1 KB.
@@ -299,6 +299,7 @@ struct StepPack {
     static constexpr int KU = (MODE == MODE_FP8) ? 16 : 8;            // k per unit
     static constexpr int UK = 4;                                      // units per row and step
     static constexpr int HK = (MODE == MODE_X3 ? 2 : 4) * KU;         // k per step
+    static_assert(MODE == MODE_X3 || MODE == MODE_FP8, "the forms whose tiles take turns");
     static constexpr int GROUPS = HK / KU;                            // groups of KU k per row and step
     static constexpr int ROWS = 256;
     static constexpr int CHUNK = ROWS * UK * 16;                      // bytes
@@ -750,7 +751,7 @@ struct TileParts<CF, true> {
 };
 
 // A-side packing into steps, KU consecutive k (k0 ..) of row r: bytes copied
-// for codes, split into a high and a low unit for x3; zero beyond R and K.
+// for e4m3 codes, split into a high and a low unit for x3; zero beyond R and K.
 // Vector loads as in pack_row_group (e4m3: 16 codes, when vec says so).
 template <int MODE>
 __device__ __forceinline__ void step_row_group(const void* X, int64_t ldx, int R, int K, char* P, int Kp, int r, int k0,
@@ -786,11 +787,7 @@ __device__ __forceinline__ void step_row_group(const void* X, int64_t ldx, int R
         } else if (r < R) {
 #pragma unroll
             for (int e = 0; e < SP::KU; ++e)
-                if (k0 + e < K) {
-                    const uint32_t c = ES == 2 ? reinterpret_cast<const uint16_t*>(src)[e]
-                                               : reinterpret_cast<const uint8_t*>(src)[e];
-                    w[e * ES / 4] |= c << (8 * (e * ES % 4));
-                }
+                if (k0 + e < K) w[e / 4] |= (uint32_t)reinterpret_cast<const uint8_t*>(src)[e] << (8 * (e % 4));
         }
         *reinterpret_cast<u32x4*>(dst + pk_slot<SP::UK>(row, g) * 16) = w;
     }
@@ -828,7 +825,7 @@ __device__ __forceinline__ void step_col_block(const void* X, int64_t ldx, int K
             u32x4 w = {0, 0, 0, 0};
 #pragma unroll
             for (int e = 0; e < SP::KU; ++e)
-                w[e * ES / 4] |= __float_as_uint(tile[kk + e][nn]) << (8 * (e * ES % 4));
+                w[e / 4] |= __float_as_uint(tile[kk + e][nn]) << (8 * (e % 4));
             *reinterpret_cast<u32x4*>(dst + pk_slot<SP::UK>(row, g) * 16) = w;
         }
     }
@@ -912,56 +909,41 @@ __device__ __forceinline__ void packed_tile_range(const PackedArgs& a, int m0, i
     // written by the same kernel and may alias the scales.)
     // A wave tile no larger than a 128 x 128 scale tile lies inside one (tiles
     // start at multiples of their size), so one product serves all its blocks.
-    constexpr bool one_scale = CF::WTM <= 128 && CF::WTN <= 128;
-    constexpr int SM = one_scale ? 1 : CF::TM, SN = one_scale ? 1 : CF::TN;
-    // e4m3 with one product per wave: the powers of two of sA and sB go to the
+    static_assert(!scaled || (CF::WTM <= 128 && CF::WTN <= 128), "one scale product per wave");
+    // e4m3: the powers of two of sA and sB go to the
     // matrix core as its block scales (e8a, e8b), and acc is kept in units of
     // the product of their mantissas, m = fl32(ma * mb) = fl32(sA * sB) / 2^E;
     // with power-of-two scales m stays 1 and acc is never rescaled.
-    constexpr bool mx = scaled && one_scale && CF::MODE == MODE_FP8;
-    // raw: sa_next and sc_next hold the next block's two scales as loaded
-    constexpr bool raw = mx || (scaled && CF::TURNS);
-    static_assert(!CF::TURNS || one_scale, "one scale product per wave");
+    constexpr bool mx = scaled && CF::MODE == MODE_FP8;
+    static_assert(!CF::TURNS || !scaled || mx, "scaled tiles that take turns are e4m3");
     int kb_cur = (p0 * CF::BK) / 128;
-    float sc_cur[SM][SN], sc_next[SM][SN];  // mx: sc_cur holds m, sc_next the raw sB
+    float sc_cur, sc_next;  // mx: sc_cur holds m, sc_next the raw sB (sa_next the raw sA)
     int e8a = 127, e8b = 127;
     float sa_next = 1.f;
-    auto load_scales = [&](int kb, float (&dst)[SM][SN]) {
-        if constexpr (raw) {
-            if constexpr (CF::TURNS) block_scales_scalar(a, m0 + wm0, n0 + wn0, kb, sa_next, dst[0][0]);
-            else block_scales(a, m0 + wm0, n0 + wn0, kb, sa_next, dst[0][0]);
-        } else {
-#pragma unroll
-            for (int i = 0; i < SM; ++i)
-#pragma unroll
-                for (int j = 0; j < SN; ++j)
-                    dst[i][j] = block_scale(a, m0 + wm0 + CF::MS * i, n0 + wn0 + CF::MS * j, kb);
-        }
+    auto load_scales = [&](int kb, float& dst) {
+        if constexpr (mx && CF::TURNS) block_scales_scalar(a, m0 + wm0, n0 + wn0, kb, sa_next, dst);
+        else if constexpr (mx) block_scales(a, m0 + wm0, n0 + wn0, kb, sa_next, dst);
+        else dst = block_scale(a, m0 + wm0, n0 + wn0, kb);
     };
-    // the unit of the block whose raw scales are sa_next and sc_next: their product
-    // (mx: of the mantissas; the powers of two go to ea and eb)
+    // the unit of the block whose raw scales are sa_next and sc_next (mx): the product of
+    // their mantissas; the powers of two go to ea and eb
     auto unit = [&](int& ea, int& eb) {
-        if constexpr (!mx) return sa_next * sc_next[0][0];
         float ma, mb;
         split_scale(sa_next, ea, ma);
-        split_scale(sc_next[0][0], eb, mb);
+        split_scale(sc_next, eb, mb);
         return ma * mb;
     };
     // issued before the first panels, so the first panel's wait covers them
     if constexpr (scaled) {
-        if constexpr (raw) {
-            load_scales(kb_cur, sc_next);
-        } else {
-            load_scales(kb_cur, sc_cur);
-        }
+        load_scales(kb_cur, mx ? sc_next : sc_cur);
     }
 
     // Pipeline: panels p go to stage p % NS; NS - 1 panels are in flight.
     constexpr int NS = CF::NS, L = AL::LOADS + BL::LOADS;
     static_assert((NS - 2) * L <= 63, "vmcnt holds at most 63");
     for (int p = 0; p < NS - 1 && p < npanel; ++p) issue(p, lds + p * CF::LDS_STAGE);
-    bool unit_one = false;    // raw: the current unit is 1
-    bool first_block = true;  // raw: the unit of the first block is set at its first panel
+    bool unit_one = false;    // mx: the current unit is 1
+    bool first_block = true;  // mx: the unit of the first block is set at its first panel
     auto prefetch = [&](int s) {  // during panel s: the scales of panel s + 1 if it opens a block
         if (!scaled || (s + 1 >= npanel && !CF::TURNS)) return;
         const int kb = ((p0 + min(s + 1, npanel - 1)) * CF::BK) / 128;
@@ -972,18 +954,18 @@ __device__ __forceinline__ void packed_tile_range(const PackedArgs& a, int m0, i
     auto rescale = [&](int s) {
         if (!scaled) return;
         const int kb = ((p0 + s) * CF::BK) / 128;
-        if constexpr (raw) {
+        if constexpr (mx) {
             if (first_block) {
                 first_block = false;
-                sc_cur[0][0] = unit(e8a, e8b);
-                unit_one = __builtin_amdgcn_readfirstlane(__float_as_uint(sc_cur[0][0])) == 0x3f800000u;
+                sc_cur = unit(e8a, e8b);
+                unit_one = __builtin_amdgcn_readfirstlane(__float_as_uint(sc_cur)) == 0x3f800000u;
                 return;
             }
             if (kb == kb_cur) return;
             kb_cur = kb;
-            if constexpr (mx && CF::TURNS) {
+            if constexpr (CF::TURNS) {
                 // two powers of two after two powers of two: only the exponents move
-                const uint32_t ua = __float_as_uint(sa_next), ub = __float_as_uint(sc_next[0][0]);
+                const uint32_t ua = __float_as_uint(sa_next), ub = __float_as_uint(sc_next);
                 const uint32_t ea = ua >> 23, eb = ub >> 23;
                 if (unit_one && ((ua | ub) & 0x007fffffu) == 0 && ea - 1u < 254u && eb - 1u < 254u) {
                     e8a = (int)ea;
@@ -996,11 +978,11 @@ __device__ __forceinline__ void packed_tile_range(const PackedArgs& a, int m0, i
                 const uint32_t um = __builtin_amdgcn_readfirstlane(__float_as_uint(m));
                 unit_one = um == 0x3f800000u;
                 // the same finite, non-zero unit again: nothing to divide
-                if (um == __builtin_amdgcn_readfirstlane(__float_as_uint(sc_cur[0][0])) &&
+                if (um == __builtin_amdgcn_readfirstlane(__float_as_uint(sc_cur)) &&
                     (um & 0x7fffffffu) - 1u < 0x7f7fffffu)
                     return;
             }
-            const float ratio = sc_cur[0][0] / m;
+            const float ratio = sc_cur / m;
             if (ratio != 1.f) {
 #pragma unroll
                 for (int i = 0; i < CF::TM; ++i)
@@ -1009,35 +991,21 @@ __device__ __forceinline__ void packed_tile_range(const PackedArgs& a, int m0, i
 #pragma unroll
                         for (int r = 0; r < CF::AR; ++r) acc[i][j][r] *= ratio;
             }
-            sc_cur[0][0] = m;
+            sc_cur = m;
             return;
         }
         if (s == 0 || kb == kb_cur) return;
-        if constexpr (one_scale) {
-            // one product per wave: nothing to do when it does not change (acc * 1 == acc)
-            const float ratio = sc_cur[0][0] / sc_next[0][0];
-            if (ratio != 1.f) {
-#pragma unroll
-                for (int i = 0; i < CF::TM; ++i)
-#pragma unroll
-                    for (int j = 0; j < CF::TN; ++j)
-#pragma unroll
-                        for (int r = 0; r < CF::AR; ++r) acc[i][j][r] *= ratio;
-            }
-        } else {
+        // nothing to do when the product does not change (acc * 1 == acc)
+        const float ratio = sc_cur / sc_next;
+        if (ratio != 1.f) {
 #pragma unroll
             for (int i = 0; i < CF::TM; ++i)
 #pragma unroll
-                for (int j = 0; j < CF::TN; ++j) {
-                    const float ratio = sc_cur[i][j] / sc_next[i][j];
+                for (int j = 0; j < CF::TN; ++j)
 #pragma unroll
                     for (int r = 0; r < CF::AR; ++r) acc[i][j][r] *= ratio;
-                }
         }
-#pragma unroll
-        for (int i = 0; i < SM; ++i)
-#pragma unroll
-            for (int j = 0; j < SN; ++j) sc_cur[i][j] = sc_next[i][j];
+        sc_cur = sc_next;
         kb_cur = kb;
     };
     if constexpr (CF::TURNS) {
@@ -1195,7 +1163,7 @@ __device__ __forceinline__ void packed_tile_range(const PackedArgs& a, int m0, i
         }
     }
 
-    epi(acc, [&](int i, int j) { return scaled ? sc_cur[i % SM][j % SN] : 1.f; }, wm0, wn0, lane);
+    epi(acc, [&](int, int) { return scaled ? sc_cur : 1.f; }, wm0, wn0, lane);
 }
 
 // One whole macro-tile (all K panels) with the standard epilogue.
