@@ -136,8 +136,8 @@ int tgemm_with_schedule(int64_t M, int64_t N, int64_t K, float alpha,
  * partial.  dtype: TGEMM_BF16 (A, B are uint16 bf16 patterns) or
  * TGEMM_FP8_E4M3 (A, B are bytes).  scaleA and scaleB are device pointers and
  * must not be NULL when A and B are read.  Scales must be positive normal
- * floats (packed schedules keep the running sum divided by the current scale
- * product).
+ * floats and must not overlap C; their products, formed in float32, may lie
+ * any distance apart along K.
  */
 int tgemm_scaled(int64_t M, int64_t N, int64_t K, float alpha,
                  const void* A, int64_t lda, const float* scaleA,

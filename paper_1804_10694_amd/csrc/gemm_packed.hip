@@ -142,6 +142,7 @@ struct SkPartial {
     const SkArgs& k;
     int t, v, m0, n0;
     int* flag;  // LDS word: this workgroup sums the tile
+    bool again = false;  // bf16: earlier sums of the range, in another unit (unit_run), are in its slot
 
     __device__ __forceinline__ float* slot(int u) const
     {
@@ -157,32 +158,49 @@ struct SkPartial {
             slot(u) + ((wave * CF::TM + i) * CF::TN + j) * CF::AR * 64, 0, CF::AR * 64 * 4, 0x00020000);
     }
 
+    // A wave's sums, in true units, into this range's slot (again: added to what it holds).
+    template <class SC>
+    __device__ __forceinline__ void write_slot(typename CF::Acc (&acc)[CF::TM][CF::TN], const SC& sc, int wave,
+                                               int lane) const
+    {
+#pragma unroll
+        for (int i = 0; i < CF::TM; ++i)
+#pragma unroll
+            for (int j = 0; j < CF::TN; ++j) {
+                const float f = sc(i, j);
+                const __amdgpu_buffer_rsrc_t rs = block(v, wave, i, j);
+#pragma unroll
+                for (int r = 0; r < CF::AR; r += 4) {
+                    f32x4 x;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) x[e] = f * acc[i][j][r + e];
+                    if (again)
+                        x += __builtin_bit_cast(
+                            f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16 + r * 256, 0, kSc1));
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), rs, lane * 16 + r * 256, 0,
+                                                           kSc1);
+                }
+            }
+        __builtin_amdgcn_s_waitcnt(0);  // this thread's stores have completed
+    }
+
     template <class SC>
     __device__ __forceinline__ void operator()(typename CF::Acc (&acc)[CF::TM][CF::TN], const SC& sc, int wm0,
-                                               int wn0, int lane) const
+                                               int wn0, int lane, bool more) const
     {
         asm volatile("" : "+v"(lane));  // keep the slot addresses out of the main loop
         const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        if (more) {
+            write_slot(acc, sc, wave, lane);
+            return;
+        }
         const int u0 = sk_owner(k, t * k.panels), u1 = sk_owner(k, (t + 1) * k.panels - 1);
-        if (threadIdx.x == 0) *flag = __hip_atomic_load(&k.cnt[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == u1 - u0;
+        if (threadIdx.x == 0)
+            *flag = !again && __hip_atomic_load(&k.cnt[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == u1 - u0;
         __syncthreads();
         if (!__builtin_amdgcn_readfirstlane(*flag)) {
-#pragma unroll
-            for (int i = 0; i < CF::TM; ++i)
-#pragma unroll
-                for (int j = 0; j < CF::TN; ++j) {
-                    const float f = sc(i, j);
-                    const __amdgpu_buffer_rsrc_t rs = block(v, wave, i, j);
-#pragma unroll
-                    for (int r = 0; r < CF::AR; r += 4) {
-                        u32x4 x;
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) x[e] = __float_as_uint(f * acc[i][j][r + e]);
-                        __builtin_amdgcn_raw_buffer_store_b128(x, rs, lane * 16 + r * 256, 0, kSc1);
-                    }
-                }
-            __builtin_amdgcn_s_waitcnt(0);  // this thread's partial stores have completed ...
-            __syncthreads();                // ... and every thread's: the partial is complete
+            write_slot(acc, sc, wave, lane);
+            __syncthreads();  // every thread's stores have completed: the partial is complete
             if (threadIdx.x == 0) *flag = atomicAdd(&k.cnt[t], 1) == u1 - u0;
             __syncthreads();
             if (!__builtin_amdgcn_readfirstlane(*flag)) return;
@@ -205,7 +223,7 @@ struct SkPartial {
 #pragma unroll
                 for (int r = 0; r < CF::AR; ++r) s[q][r] = 0.f;
             for (int u = u0; u <= u1; ++u) {
-                if (u == v) {
+                if (u == v && !again) {
 #pragma unroll
                     for (int q = 0; q < FB; ++q) {
                         const int i = (b0 + q) / CF::TN, j = (b0 + q) % CF::TN;
@@ -250,10 +268,10 @@ struct SkStore {
     bool is_whole;
     template <class SC>
     __device__ __forceinline__ void operator()(typename CF::Acc (&acc)[CF::TM][CF::TN], const SC& sc, int wm0,
-                                               int wn0, int lane) const
+                                               int wn0, int lane, bool more) const
     {
         if (is_whole) whole(acc, sc, wm0, wn0, lane);
-        else part(acc, sc, wm0, wn0, lane);
+        else part(acc, sc, wm0, wn0, lane, more);
     }
 };
 
@@ -281,10 +299,19 @@ __global__ void __launch_bounds__(CF::NT, CF::WAVES_PER_EU) packed_sk_kernel(Pac
         const int m0 = tc.tm * CF::BM, n0 = tc.tn * CF::BN;
         const SkStore<CF> epi{TileStore<CF>{a, m0, n0}, SkPartial<CF>{a, k, t, v, m0, n0, &flag},
                               pb == 0 && pe == k.panels};
-        if ((CF::MODE == MODE_BF16 || CF::MODE == MODE_FP8) && a.sA)
+        if (CF::MODE == MODE_BF16 && a.sA) {
+            int p = pb + packed_tile_range<CF, AL, BL, OP, true>(a, m0, n0, lds, typename AL::Geom(), pb, pe - pb, epi);
+            SkStore<CF> rest = epi;
+            rest.part.again = rest.whole.again = true;
+            while (__builtin_expect(p < pe, 0)) {  // sums in other units
+                __syncthreads();
+                p += packed_tile_range<CF, AL, BL, OP, true>(a, m0, n0, lds, typename AL::Geom(), p, pe - p, rest);
+            }
+        } else if (CF::MODE == MODE_FP8 && a.sA) {
             packed_tile_range<CF, AL, BL, OP, true>(a, m0, n0, lds, typename AL::Geom(), pb, pe - pb, epi);
-        else
+        } else {
             packed_tile_range<CF, AL, BL, OP, false>(a, m0, n0, lds, typename AL::Geom(), pb, pe - pb, epi);
+        }
         if (!all) it += pe - pb;
         __syncthreads();  // every wave is done with the LDS stages (and the flag) before the next tile
     }

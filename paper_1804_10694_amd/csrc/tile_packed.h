@@ -833,20 +833,22 @@ __device__ __forceinline__ void step_col_block(const void* X, int64_t ldx, int K
 
 // Epilogue of a whole tile: C = alpha * scale * acc (+ beta * C), predicated
 // only on partial tiles.  sc(i, j) is the scale product that multiplies the
-// sums of block (i, j) (1 for unscaled forms).
+// sums of block (i, j) (1 for unscaled forms).  again: earlier sums of the tile
+// are in C already.
 template <class CF>
 struct TileStore {
     const PackedArgs& a;
     int m0, n0;
+    bool again = false;
     template <class SC>
     __device__ __forceinline__ void operator()(typename CF::Acc (&acc)[CF::TM][CF::TN], const SC& sc, int wm0,
-                                               int wn0, int lane) const
+                                               int wn0, int lane, bool = false) const
     {
         // the addresses below are computed here, not hoisted out of a loop over
         // tiles where they would hold registers through the main loop
         asm volatile("" : "+v"(lane));
         write_c<CF::TM, CF::TN, CF::AR, 16, CF::MS>(
-            a.C, a.ldc, a.M, a.N, a.beta, CF::out_row(0, lane), CF::out_col(lane),
+            a.C, a.ldc, a.M, a.N, again ? 1.f : a.beta, CF::out_row(0, lane), CF::out_col(lane),
             [&](int i, int j, float (&v)[CF::AR]) {
                 const float f = a.alpha * sc(i, j);
 #pragma unroll
@@ -860,6 +862,59 @@ struct TileStore {
     }
 };
 
+// Whether sums may move between units of these biased exponents: both those of
+// normal numbers and at most 2^24 apart.
+__host__ __device__ constexpr bool same_unit_range(int e0, int e1)
+{
+    return e0 > 0 && e0 < 255 && e1 > 0 && e1 < 255 && e1 - e0 <= 24 && e0 - e1 <= 24;
+}
+static_assert(same_unit_range(127, 151) && !same_unit_range(127, 152) && !same_unit_range(40, 10) &&
+                  !same_unit_range(0, 0) && !same_unit_range(255, 255),
+              "units");
+
+// bf16: of panels [p, p + np) of the tile, how many can share sums.  The sums stand
+// in units of the current K block's scale product, and moved on to a product far
+// from it they would overflow or vanish beside sums that float32 holds (2^116, then
+// 2^-80, gave NaN), so they stay within 2^24 of the product they began with; the
+// next K block begins new ones.  One wave looks, 64 K blocks at a time, while the
+// tile's first panels are on their way: 2048 x 4096 x 4096 98.8 -> 99.9 us, 1000^3
+// 24.7 -> 25.2, 5000^2 x 300 49.8 -> 52.  (The caller's loop over the runs is apart
+// from the first of them: in one loop its state cost the main loop another 2 to 4%.)
+// `word` is a part of the panels' LDS that none of them goes to, free again after the
+// next barrier (a second LDS object in the kernel makes the compiler wait for every
+// panel load in flight before each LDS read: 1.4 times the time).
+template <class CF>
+__device__ __forceinline__ int unit_run(const PackedArgs& a, int m0, int n0, int p, int np, int* word)
+{
+    constexpr int PB = 128 / CF::BK;  // panels per K block
+    if (threadIdx.x < 64) {
+        const int lane = threadIdx.x;
+        const int kb0 = p / PB, end = (p + np + PB - 1) / PB;
+        int run = np;
+        for (int k = kb0; k < end; k += 64) {
+            const int kk = min(k + lane, end - 1);
+            bool in = true;
+            for (int r = m0 / 128; r <= min(m0 + CF::BM - 1, a.M - 1) / 128; ++r)
+                for (int c = n0 / 128; c <= min(n0 + CF::BN - 1, a.N - 1) / 128; ++c) {
+                    const float s0 = a.sA[r * a.lds_a + kb0] * a.sB[kb0 * a.lds_b + c];
+                    const float s1 = a.sA[r * a.lds_a + kk] * a.sB[kk * a.lds_b + c];
+                    in = in && same_unit_range((__float_as_uint(s0) >> 23) & 0xff, (__float_as_uint(s1) >> 23) & 0xff);
+                }
+            const uint64_t out = __ballot(!in && kk > kb0);
+            if (out) {
+                run = (k + __ffsll((unsigned long long)out) - 1) * PB - p;
+                break;
+            }
+        }
+        if (lane == 0) *word = run;
+        wait_lds_reads();  // the store, too
+    }
+    lds_barrier();
+    const int run = __builtin_amdgcn_readfirstlane(*word);
+    wait_lds_reads();
+    return run;
+}
+
 // Panels [p0, p0 + np) of one BM x BN macro-tile at (m0, n0) of problem `a`;
 // `lds` holds CF::LDS_BYTES.  AL and BL bring the A and B panels into an LDS
 // stage (A first, B at offset NARR * LDS_A), each issuing a fixed number of
@@ -871,10 +926,12 @@ struct TileStore {
 // `lds` with a barrier.
 // SCALED: a.sA and a.sB hold per-tile scales (bf16 and e4m3 only; the caller
 // branches on a.sA once, so each loop is compiled for one case).
+// Returns how many of the panels were summed, all but for scaled bf16 (unit_run):
+// there EPI is told that more follow, and the caller calls again for the rest.
 template <class CF, class AL, class BL, class OP, bool SCALED, class EPI>
-__device__ __forceinline__ void packed_tile_range(const PackedArgs& a, int m0, int n0, char* lds,
-                                                  const typename AL::Geom& geom, int p0, int np,
-                                                  const EPI& epi)
+__device__ __forceinline__ int packed_tile_range(const PackedArgs& a, int m0, int n0, char* lds,
+                                                 const typename AL::Geom& geom, int p0, int np,
+                                                 const EPI& epi)
 {
     const int t = threadIdx.x, lane = t & 63;
     // the wave index is uniform; readfirstlane lets the compiler keep it (and the
@@ -895,7 +952,6 @@ __device__ __forceinline__ void packed_tile_range(const PackedArgs& a, int m0, i
 #pragma unroll
             for (int r = 0; r < CF::AR; ++r) acc[i][j][r] = 0.f;
 
-    const int npanel = np;
     auto issue = [&](int panel, char* stage) {  // panel: index within the range
         al.issue(p0 + panel, stage);
         bl.issue(p0 + panel, stage + CF::NARR * CF::LDS_A);
@@ -941,7 +997,13 @@ __device__ __forceinline__ void packed_tile_range(const PackedArgs& a, int m0, i
     // Pipeline: panels p go to stage p % NS; NS - 1 panels are in flight.
     constexpr int NS = CF::NS, L = AL::LOADS + BL::LOADS;
     static_assert((NS - 2) * L <= 63, "vmcnt holds at most 63");
-    for (int p = 0; p < NS - 1 && p < npanel; ++p) issue(p, lds + p * CF::LDS_STAGE);
+    for (int p = 0; p < NS - 1 && p < np; ++p) issue(p, lds + p * CF::LDS_STAGE);
+    constexpr bool runs = scaled && !mx;
+    const int npanel = [&] {
+        if constexpr (runs)
+            return unit_run<CF>(a, m0, n0, p0, np, reinterpret_cast<int*>(lds + (NS - 1) * CF::LDS_STAGE));
+        else return np;
+    }();
     bool unit_one = false;    // mx: the current unit is 1
     bool first_block = true;  // mx: the unit of the first block is set at its first panel
     auto prefetch = [&](int s) {  // during panel s: the scales of panel s + 1 if it opens a block
@@ -1163,7 +1225,14 @@ __device__ __forceinline__ void packed_tile_range(const PackedArgs& a, int m0, i
         }
     }
 
-    epi(acc, [&](int, int) { return scaled ? sc_cur : 1.f; }, wm0, wn0, lane);
+    auto unit_of = [&](int, int) { return scaled ? sc_cur : 1.f; };
+    if constexpr (runs) {
+        if (npanel < np) wait_vmcnt<0>();  // first panels past the run may still be on their way
+        epi(acc, unit_of, wm0, wn0, lane, npanel < np);
+    } else {
+        epi(acc, unit_of, wm0, wn0, lane, false);
+    }
+    return npanel;
 }
 
 // One whole macro-tile (all K panels) with the standard epilogue.
@@ -1173,7 +1242,17 @@ __device__ __forceinline__ void packed_tile(const PackedArgs& a, int m0, int n0,
                                             const typename AL::Geom& geom = typename AL::Geom())
 {
     const int np = (a.K + CF::BK - 1) / CF::BK;
-    if ((CF::MODE == MODE_BF16 || CF::MODE == MODE_FP8) && a.sA)
+    if constexpr (CF::MODE == MODE_BF16)
+        if (a.sA) {
+            int p = packed_tile_range<CF, AL, BL, OP, true>(a, m0, n0, lds, geom, 0, np, TileStore<CF>{a, m0, n0});
+            while (__builtin_expect(p < np, 0)) {  // sums in other units
+                __syncthreads();
+                p += packed_tile_range<CF, AL, BL, OP, true>(a, m0, n0, lds, geom, p, np - p,
+                                                             TileStore<CF>{a, m0, n0, true});
+            }
+            return;
+        }
+    if (CF::MODE == MODE_FP8 && a.sA)
         packed_tile_range<CF, AL, BL, OP, true>(a, m0, n0, lds, geom, 0, np, TileStore<CF>{a, m0, n0});
     else
         packed_tile_range<CF, AL, BL, OP, false>(a, m0, n0, lds, geom, 0, np, TileStore<CF>{a, m0, n0});
