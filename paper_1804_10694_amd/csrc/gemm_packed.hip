@@ -224,6 +224,9 @@ struct SkPartial {
                 for (int r = 0; r < CF::AR; ++r) s[q][r] = 0.f;
             for (int u = u0; u <= u1; ++u) {
                 if (u == v && !again) {
+                    // rounded before it is added, as the sums in the slots are: no fma, or the
+                    // result would depend on which workgroup finishes last
+#pragma clang fp contract(off)
 #pragma unroll
                     for (int q = 0; q < FB; ++q) {
                         const int i = (b0 + q) / CF::TN, j = (b0 + q) % CF::TN;
