@@ -64,10 +64,17 @@ struct G2Cfg {
 };
 
 // Rows of B or D from one on: what follows in bytes (0 past the last row or column).
+// A panel's range and the lanes' offsets into it are unsigned 32-bit numbers up to 2^32.
 struct G2Src {
     __amdgpu_buffer_rsrc_t r;
     uint32_t row_bytes;
 };
+constexpr int64_t kG2RowFloats = INT32_MAX / 64;  // longest rows of B and D
+template <class G>
+constexpr bool kG2Reach = G::BK * 4 * kG2RowFloats <= (int64_t)UINT32_MAX &&
+                          (G::BK - 1) * 4 * kG2RowFloats + 128 * (G::template P2<2>::TN + 1) <= (int64_t)UINT32_MAX;
+static_assert(kG2Reach<G2Cfg<MODE_F32, 256, 64>> && kG2Reach<G2Cfg<MODE_X3, 256, 64>>,
+              "a panel of the longest rows, and its last row's last lane");
 
 // Rows k0 .. k0 + BK of the columns from n0 on of a K x N matrix.
 template <int BK>
@@ -297,9 +304,8 @@ extern "C" int tgemm_gemm2(int64_t M, int64_t N1, int64_t N2, int64_t K, float a
     if (reads) {
         if (!A || !B || !D) return TGEMM_INVALID_VALUE;
         if (lda < K || ldb < N1 || ldd < N2) return TGEMM_INVALID_VALUE;
-        // a 64-row block of A and a 16-row panel of B or D within a buffer's 32-bit offsets
-        if (64 * lda * 4 > INT32_MAX || 16 * ldb * 4 > INT32_MAX || 16 * ldd * 4 > INT32_MAX)
-            return TGEMM_NOT_SUPPORTED;
+        // a 64-row block of A within a buffer's 31-bit offsets, a panel of B or D within 32 bits
+        if (64 * lda * 4 > INT32_MAX || ldb > kG2RowFloats || ldd > kG2RowFloats) return TGEMM_NOT_SUPPORTED;
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
     int rc = ensure_device(s);
