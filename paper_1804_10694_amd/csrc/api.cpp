@@ -156,14 +156,6 @@ int run_gemm(int id, int64_t M, int64_t N, int64_t K, float alpha, const void* A
     return launch_gemm(d, a, stream) == hipSuccess ? TGEMM_SUCCESS : TGEMM_LAUNCH_FAILED;
 }
 
-// A packing workspace that could not be had, for a bf16 or e4m3 problem that
-// direct tiles serve well enough.
-static bool no_room(int rc, int dtype, int64_t M, int64_t N, int64_t K)
-{
-    return rc == TGEMM_ALLOC_FAILED && (dtype == TGEMM_BF16 || dtype == TGEMM_FP8_E4M3) &&
-           !scaled_needs_packing(M, N, K);
-}
-
 // A float32 problem as the selection chose: on a register tile where the rule
 // names one that serves the operands, else on the schedule; a stream-K form that
 // cannot have its workspace gives way to the schedule it was chosen over.
@@ -233,7 +225,7 @@ int tgemm(int64_t M, int64_t N, int64_t K, float alpha, const void* A, int64_t l
         // in-place one whose rows lie past the reach of its buffer offsets: use the
         // rule's schedule without packing instead
         if (rc != TGEMM_CAPTURE_UNPLANNED && !(rc == TGEMM_NOT_SUPPORTED && (schedule(ch.id).inplace || ch.unshared >= 0)) &&
-            !no_room(rc, dtype, M, N, K))
+            !(rc == TGEMM_ALLOC_FAILED && packing_optional(ch.id, M, N, K, dtype, vok)))
             return rc;
         if ((rc = direct_schedule(M, N, K, dtype, vok, &ch)) != TGEMM_SUCCESS) return rc;
     }
@@ -283,7 +275,9 @@ int tgemm_scaled(int64_t M, int64_t N, int64_t K, float alpha, const void* A, in
     if (rc != TGEMM_SUCCESS) return rc;
     rc = run_scaled(M, N, K, alpha, A, lda, scaleA, B, ldb, scaleB, beta, C, ldc, dtype, ch.id,
                     ch.group_m, ch.xcd_remap, s);
-    if (rc != TGEMM_CAPTURE_UNPLANNED && !no_room(rc, dtype, M, N, K)) return rc;
+    if (rc != TGEMM_CAPTURE_UNPLANNED &&
+        !(rc == TGEMM_ALLOC_FAILED && packing_optional(ch.id, M, N, K, dtype, vok)))
+        return rc;
     if ((rc = direct_schedule(M, N, K, dtype, vok, &ch)) != TGEMM_SUCCESS) return rc;
     return run_scaled(M, N, K, alpha, A, lda, scaleA, B, ldb, scaleB, beta, C, ldc, dtype, ch.id,
                       ch.group_m, ch.xcd_remap, s);

@@ -838,7 +838,7 @@ extern "C" int tgemm_noalloc(int64_t M, int64_t N, int64_t K, float alpha, const
     }
     if (!packed_k_ok(K, dtype)) return TGEMM_NOT_SUPPORTED;
     if (packed_workspace_bytes(M, N, K, dtype) > (size_t)TGEMM_NOALLOC_SCRATCH_BYTES) {
-        if (!scaled || scaled_needs_packing(M, N, K)) return TGEMM_SCRATCH_TOO_SMALL;
+        if (!packing_optional(ch.id, M, N, K, dtype, vok)) return TGEMM_SCRATCH_TOO_SMALL;
         if ((rc = direct_schedule(M, N, K, dtype, vok, &ch)) != TGEMM_SUCCESS) return rc;
         return run_scaled(M, N, K, alpha, A, lda, nullptr, B, ldb, nullptr, beta, C, ldc, dtype, ch.id, ch.group_m,
                           ch.xcd_remap, s);

@@ -321,12 +321,15 @@ static int table_rule(int64_t M, int64_t N, int64_t K, int dtype, bool vec_allow
     return direct_schedule(M, N, K, dtype, vec_allowed, out);
 }
 
-// bf16 and e4m3 sizes whose packing workspace a caller without one must refuse;
-// the others can run direct tiles.
-bool scaled_needs_packing(int64_t M, int64_t N, int64_t K)
+// Large and deep sizes must have the workspace; so must a schedule that a policy
+// names (forced, tuned or predicted).
+bool packing_optional(int id, int64_t M, int64_t N, int64_t K, int dtype, bool vec_allowed)
 {
+    if (dtype != TGEMM_BF16 && dtype != TGEMM_FP8_E4M3) return false;
     auto tiles = [&](int b) { return ((M + b - 1) / b) * ((N + b - 1) / b); };
-    return K >= 512 && (tiles(256) >= 128 || tiles(128) >= 192);
+    if (K >= 512 && (tiles(256) >= 128 || tiles(128) >= 192)) return false;
+    Choice rule;
+    return default_schedule(M, N, K, dtype, vec_allowed, &rule) == TGEMM_SUCCESS && rule.id == id;
 }
 
 // The stream-K form that beats schedule `id`, the table rule's, because it shares

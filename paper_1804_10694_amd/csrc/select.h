@@ -34,7 +34,9 @@ bool costmodel_cached(int64_t M, int64_t N, int64_t K, int dtype, bool vec_allow
 // Built-in rule only (also the fallback of the other policies).
 int default_schedule(int64_t M, int64_t N, int64_t K, int dtype, bool vec_allowed, Choice* out);
 
-bool scaled_needs_packing(int64_t M, int64_t N, int64_t K);
+// bf16 and e4m3: whether `id` is the packed schedule that the built-in rule names for a
+// problem that direct tiles serve as well where no workspace can be had.
+bool packing_optional(int id, int64_t M, int64_t N, int64_t K, int dtype, bool vec_allowed);
 
 // Built-in rule restricted to schedules that need no workspace.
 int direct_schedule(int64_t M, int64_t N, int64_t K, int dtype, bool vec_allowed, Choice* out);
