@@ -31,9 +31,9 @@ namespace {
 // sixteen waves over K gain nothing: four already use every SIMD of a CU.
 template <int MODE, bool AK, bool BK>
 struct RegTiles {
-    using T0 = RCfg<MODE, AK, BK, 1, 1, 1, 1, 4, 16, 6>;
-    using T1 = RCfg<MODE, AK, BK, 2, 1, 1, 1, 4, 16, 4>;
-    using T2 = RCfg<MODE, AK, BK, 2, 2, 1, 1, 4, 16, 2>;
+    using T0 = RCfg<MODE, AK, BK, 1, 1, 6>;
+    using T1 = RCfg<MODE, AK, BK, 2, 1, 4>;
+    using T2 = RCfg<MODE, AK, BK, 2, 2, 2>;
 };
 
 template <class CF>

@@ -221,7 +221,7 @@ int gemm_f32(int64_t M, int64_t N, int64_t K, const float* A, int64_t lda, const
 // gradient with the bias gradient (column sums of the same operand registers)
 // beside the gradient of its input with the ReLU mask, and Adam.
 template <bool AK, bool BK>
-using MlpTile = RCfg<MODE_F32, AK, BK, 1, 1, 1, 1, 4, 16, 6>;
+using MlpTile = RCfg<MODE_F32, AK, BK, 1, 1, 6>;
 
 // Z = A W + b, through ReLU if relu.
 template <class CF>

@@ -6,19 +6,19 @@
 // tile to a workgroup and walk its K in 16-deep panels with a barrier each.  A
 // problem of a few dozen tiles then runs one wave per SIMD on a part of the
 // chip and waits out the memory latency at every panel.  Here a workgroup's
-// tile can be as small as one 32 x 32 block, WK waves take its K in turns of
-// 32, and no wave waits for another until the final sum.  An F32 MFMA takes 64
-// cycles for 8 bytes per lane, so the operand loads of a 32 x 32 block (16
-// bytes a cycle per CU with four waves, half of the L1's rate) need no LDS to
-// be shared.
+// tile can be as small as one 32 x 32 block, its four waves take its K in turns
+// of 16 (a chunk), and no wave waits for another until the final sum.  An F32
+// MFMA takes 64 cycles for 8 bytes per lane, so the operand loads of a 32 x 32
+// block (16 bytes a cycle per CU with four waves, half of the L1's rate) need no
+// LDS to be shared.
 //
 // Both operands may be stored either way: K contiguous (A row-major, B^T
 // row-major) or row contiguous (A^T row-major, B row-major), so products of
-// transposed matrices need no transposing pass.  In a chunk of 32 k, lane half
-// h takes k = 16h + 4q + e (q, e = 0..3) of its row for both operands: four
-// 16-byte loads that use the whole 128-byte line of a K-contiguous row
-// between the two halves, or sixteen 4-byte loads of which each covers two
-// 128-byte runs of 32 consecutive rows.  MFMA (q, e) pairs equal k.
+// transposed matrices need no transposing pass.  In a chunk, lane half h takes
+// k = 8h + q (q = 0..7) of its row for both operands: two 16-byte loads, which
+// between the halves use 64 contiguous bytes of a K-contiguous row, or eight
+// 4-byte loads of which each covers two 128-byte runs of 32 consecutive rows.
+// MFMA q pairs equal k.
 //
 // Edges.  Rows past the end are clamped to the last row (their sums are never
 // stored).  The chunk that holds K's end loads element by element at clamped
@@ -42,22 +42,20 @@ struct RegArgs {
     int tiles_m, tiles_n, group_m, xcd_remap;
 };
 
-// TM x TN blocks of 32 x 32 per wave, WGM x WGN waves over the tile, WK waves
-// over K; AK / BK: A / B has K contiguous.  OCC: waves per SIMD to compile for.
-template <int MODE_, bool AK_, bool BK_, int TM_, int TN_, int WGM_, int WGN_, int WK_, int CH_, int OCC_>
+// A tile of TM x TN blocks of 32 x 32; AK / BK: A / B has K contiguous.  OCC:
+// waves per SIMD to compile for.
+template <int MODE_, bool AK_, bool BK_, int TM_, int TN_, int OCC_>
 struct RCfg {
-    static constexpr int MODE = MODE_, TM = TM_, TN = TN_, WGM = WGM_, WGN = WGN_, WK = WK_, OCC = OCC_;
-    static constexpr int CH = CH_;      // k per chunk
+    static constexpr int MODE = MODE_, TM = TM_, TN = TN_, OCC = OCC_;
+    static constexpr int WK = 4;        // waves, over K
+    static constexpr int CH = 16;       // k per chunk
     static constexpr int KL = CH / 2;   // k per lane and chunk
     static constexpr bool AK = AK_, BK = BK_;
-    static constexpr int BM = 32 * TM * WGM, BN = 32 * TN * WGN;
-    static constexpr int NT = 64 * WGM * WGN * WK;
+    static constexpr int BM = 32 * TM, BN = 32 * TN;
+    static constexpr int NT = 64 * WK;
     static constexpr int AR = 16 / WK;  // sums per lane and block that a wave stores
-    // the sums of all K waves but the storing one's own share go through LDS
-    static constexpr int LDS_BYTES = WK == 1 ? 4 : WGM * WGN * WK * TM * TN * 4096;
+    static constexpr int LDS_BYTES = WK * TM * TN * 4096;  // every wave's sums
     static_assert(MODE == MODE_F32 || MODE == MODE_X3, "float32 operands");
-    static_assert(WK == 1 || WK == 2 || WK == 4 || WK == 8 || WK == 16, "16 sums per lane divide among WK waves");
-    static_assert(NT <= 1024 && LDS_BYTES <= 160 * 1024, "one workgroup");
 };
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t reg_rsrc(const char* base)
@@ -65,8 +63,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t reg_rsrc(const char* base)
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0, 0x7fffffff, 0x00020000);
 }
 
-// One operand's chunk loads for the T blocks of a wave: rows r0 + off + 32 i
-// of a matrix of R rows (off: the wave's first row inside the tile at r0).
+// One operand's chunk loads for T blocks: rows r0 + 32 i of a matrix of R rows.
 template <bool KC, int T, int CH>
 struct RegOperand {
     static constexpr int KL = CH / 2;
@@ -75,7 +72,7 @@ struct RegOperand {
     int ld, h;
     int voff[T];  // this lane's row of block i, and its first k of a chunk
 
-    __device__ __forceinline__ void init(const float* X, int64_t ldx, int r0, int off, int R, int lane)
+    __device__ __forceinline__ void init(const float* X, int64_t ldx, int r0, int R, int lane)
     {
         h = lane >> 5;
         ld4 = ldx * 4;
@@ -83,7 +80,7 @@ struct RegOperand {
         base = reinterpret_cast<const char*>(KC ? X + (int64_t)r0 * ldx : X + r0);
 #pragma unroll
         for (int i = 0; i < T; ++i) {
-            const int row = min(r0 + off + 32 * i + (lane & 31), R - 1) - r0;
+            const int row = min(r0 + 32 * i + (lane & 31), R - 1) - r0;
             voff[i] = KC ? row * ld + 4 * KL * h : row * 4 + KL * h * ld;
         }
     }
@@ -111,7 +108,7 @@ struct RegOperand {
         }
     }
 
-    // The chunk that holds K's end (left of its 32 k exist, 1 .. 31).
+    // The chunk that holds K's end (left of its k exist, 1 .. CH - 1).
     __device__ __forceinline__ void load_tail(int c, int left, float (&v)[T][KL]) const
     {
         const int k0 = c * CH;
@@ -190,14 +187,12 @@ template <class CF, bool COLSUM = false, class EPI>
 __device__ __forceinline__ void reg_tile(const RegArgs& a, int m0, int n0, char* lds, const EPI& epi)
 {
     const int t = threadIdx.x, lane = t & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int wk = wave % CF::WK, w = wave / CF::WK;
-    const int wm = (w / CF::WGN) * 32 * CF::TM, wn = (w % CF::WGN) * 32 * CF::TN;
+    const int wk = __builtin_amdgcn_readfirstlane(t >> 6);
 
     RegOperand<CF::AK, CF::TM, CF::CH> la;
     RegOperand<CF::BK, CF::TN, CF::CH> lb;
-    la.init(a.A, a.lda, m0, wm, a.M, lane);
-    lb.init(a.B, a.ldb, n0, wn, a.N, lane);
+    la.init(a.A, a.lda, m0, a.M, lane);
+    lb.init(a.B, a.ldb, n0, a.N, lane);
 
     f32x16 acc[CF::TM][CF::TN];
 #pragma unroll
@@ -254,62 +249,45 @@ __device__ __forceinline__ void reg_tile(const RegArgs& a, int m0, int n0, char*
     }
 
     RegSums<CF> s;
-    s.m0 = m0 + wm;
-    s.n0 = n0 + wn;
+    s.m0 = m0;
+    s.n0 = n0;
     s.first = wk * CF::AR;
-    if constexpr (CF::WK == 1) {
+    float* red = reinterpret_cast<float*>(lds);
+    // the four sums of a lane's group g of block b, of K wave k (one 16-byte LDS access)
+    static_assert(CF::AR == 4, "a wave stores one group of every block");
+    auto at = [&](int k, int b, int g) { return red + ((k * CF::TM * CF::TN + b) * 4 + g) * 256 + lane * 4; };
 #pragma unroll
-        for (int i = 0; i < CF::TM; ++i)
+    for (int b = 0; b < CF::TM * CF::TN; ++b)
 #pragma unroll
-            for (int j = 0; j < CF::TN; ++j)
+        for (int g = 0; g < 4; ++g)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) s.v[i][j][r] = acc[i][j][r];
-    } else {
-        // sums of a lane in groups of G: 4 (16-byte LDS accesses) where a wave's
-        // share allows it
-        constexpr int G = CF::AR >= 4 ? 4 : CF::AR;
-        float* red = reinterpret_cast<float*>(lds) + w * CF::WK * (CF::TM * CF::TN * 1024);
-        auto at = [&](int k, int b, int g) {  // group g of block b of K wave k
-            return red + ((k * CF::TM * CF::TN + b) * (16 / G) + g) * (64 * G) + lane * G;
-        };
+            for (int e = 0; e < 4; ++e) at(wk, b, g)[e] = acc[b / CF::TN][b % CF::TN][g * 4 + e];
+    __syncthreads();
 #pragma unroll
-        for (int b = 0; b < CF::TM * CF::TN; ++b)
+    for (int b = 0; b < CF::TM * CF::TN; ++b)
 #pragma unroll
-            for (int g = 0; g < 16 / G; ++g)
+        for (int r = 0; r < CF::AR; ++r) s.v[b / CF::TN][b % CF::TN][r] = 0.f;
 #pragma unroll
-                for (int e = 0; e < G; ++e) at(wk, b, g)[e] = acc[b / CF::TN][b % CF::TN][g * G + e];
-        __syncthreads();
+    for (int k = 0; k < CF::WK; ++k)
 #pragma unroll
         for (int b = 0; b < CF::TM * CF::TN; ++b)
 #pragma unroll
-            for (int r = 0; r < CF::AR; ++r) s.v[b / CF::TN][b % CF::TN][r] = 0.f;
-#pragma unroll
-        for (int k = 0; k < CF::WK; ++k)
-#pragma unroll
-            for (int b = 0; b < CF::TM * CF::TN; ++b)
-#pragma unroll
-                for (int r = 0; r < CF::AR; ++r)
-                    s.v[b / CF::TN][b % CF::TN][r] += at(k, b, (wk * CF::AR + r) / G)[r % G];
-    }
+            for (int r = 0; r < CF::AR; ++r) s.v[b / CF::TN][b % CF::TN][r] += at(k, b, wk)[r];
     if constexpr (COLSUM) {
 #pragma unroll
         for (int j = 0; j < CF::TN; ++j) cs[j] += __shfl_xor(cs[j], 32);
-        if constexpr (CF::WK > 1) {
-            float* red = reinterpret_cast<float*>(lds);
-            __syncthreads();
-            if (lane < 32)
+        __syncthreads();
+        if (lane < 32)
 #pragma unroll
-                for (int j = 0; j < CF::TN; ++j) red[(wave * CF::TN + j) * 32 + lane] = cs[j];
-            __syncthreads();
+            for (int j = 0; j < CF::TN; ++j) red[(wk * CF::TN + j) * 32 + lane] = cs[j];
+        __syncthreads();
 #pragma unroll
-            for (int j = 0; j < CF::TN; ++j) {
-                cs[j] = 0.f;
+        for (int j = 0; j < CF::TN; ++j) {
+            cs[j] = 0.f;
 #pragma unroll
-                for (int k = 0; k < CF::WK; ++k)
-                    cs[j] += red[((w * CF::WK + k) * CF::TN + j) * 32 + (lane & 31)];
-            }
+            for (int k = 0; k < CF::WK; ++k) cs[j] += red[(k * CF::TN + j) * 32 + (lane & 31)];
         }
-        if (wk == 0 && lane < 32 && wm == 0) epi.columns(cs, s, lane);
+        if (wk == 0 && lane < 32) epi.columns(cs, s, lane);
     }
     epi(s, lane);
 }
