@@ -101,6 +101,14 @@ def paths_by_grid(bench):
     return out
 
 
+def rest_grid(label):
+    """Threads of inplace_rest_kernel on the path's shape: 256 for each 128 x 128 tile, the tiles
+    past whole multiples of 256 as four quarters."""
+    m, n, _ = (int(x) for x in label.split("_", 1)[1].split("x"))
+    tiles = -(-m // 128) * -(-n // 128)
+    return 256 * (tiles + 3 * (tiles % 256))
+
+
 def match(calls, bench):
     """{label: (key, [calls])} for the calls whose main kernel grid (or, for a
     stream-K form, kernel name and tile) names one path."""
@@ -113,8 +121,9 @@ def match(calls, bench):
         elif "inplace_rest_kernel" in main["name"]:
             # f32 128 x 128 tiles and quarters of them, whichever in-place schedule is named
             for label in (lb for lb, _, p in sum(grids.values(), []) if p.get("inplace") and lb.startswith("f32")):
-                got[label].append((main, packs))
-                break
+                if rest_grid(label) == main["grid"]:
+                    got[label].append((main, packs))
+                    break
             continue
         else:
             cands = grids.get(main["grid"], [])
