@@ -59,7 +59,8 @@ typedef enum {
 typedef enum {
     TGEMM_SUCCESS = 0,
     TGEMM_INVALID_VALUE = 1,    /* bad size, leading dimension or null pointer     */
-    TGEMM_NOT_SUPPORTED = 2,    /* unknown dtype or schedule                       */
+    TGEMM_NOT_SUPPORTED = 2,    /* unknown dtype or schedule, or a size past what its
+                                   offsets or one launch (2^32 threads) reach      */
     TGEMM_LAUNCH_FAILED = 3,    /* a HIP call or kernel launch returned an error   */
     TGEMM_ALLOC_FAILED = 4,     /* device memory for a plan could not be allocated */
     TGEMM_CAPTURE_UNPLANNED = 5,/* batched call under stream capture with no plan  */
@@ -89,10 +90,11 @@ int tgemm(int64_t M, int64_t N, int64_t K, float alpha,
  * allocation).  Arguments, results and degenerate cases as tgemm, with the
  * same schedule choice except that the cost model is never run (its cached
  * answers, the tuning database and the built-in rule are used) and that a
- * stream-K choice, whose per-tile counters the library allocates, runs as its
- * whole-tile schedule (the same tiles and K panels, one workgroup per tile:
- * another summation order, so the result may differ from tgemm's in the last
- * bits; on exact-integer inputs both are exact).  A packed
+ * stream-K choice, whose per-tile counters the library allocates, is not run:
+ * one that the rule took over another schedule runs as that schedule, any other
+ * as its whole-tile schedule (the same tiles and K panels, one workgroup per
+ * tile).  Either sums in another order, so the result may differ from tgemm's
+ * in the last bits; on exact-integer inputs both are exact.  A packed
  * schedule's packing workspace is a static device array of
  * TGEMM_NOALLOC_SCRATCH_BYTES (128 MiB) in the library's code object, one per
  * device, held from the library's first use on that device until the process
@@ -102,11 +104,17 @@ int tgemm(int64_t M, int64_t N, int64_t K, float alpha,
  * the sizes rounded up to 256, Kp = K rounded up to 128 (plus 512 bytes per
  * row when that row is a multiple of 4 KB), e = 4 for F32 and
  * F32_BF16X3, 2 for BF16, 1 for FP8_E4M3: 4096 x 4096 x 2048 fits in every
- * form; larger packed problems return TGEMM_SCRATCH_TOO_SMALL before any
- * launch.  Every call on a device shares that device's array: calls that may
- * overlap on one device (different streams, or threads without ordering)
- * race, and must be serialised by the caller.  Each call writes every byte of
- * the region it reads before reading it, so no clearing is needed.
+ * form.  A problem whose schedule (tgemm_select_schedule) is a packed one that
+ * needs more returns TGEMM_SCRATCH_TOO_SMALL before any launch, also where
+ * register tiles, which need none, would serve it; except that BF16 and
+ * FP8_E4M3 problems that the rule packs with K < 512, or with fewer than 128
+ * tiles of 256 x 256 and fewer than 192 of 128 x 128, run direct tiles instead.
+ * Every call on a device shares that device's array: calls that may overlap on
+ * one device (different streams, or threads without ordering) race, and must
+ * be serialised by the caller, whatever their sizes: which of them pack is the
+ * rule's choice and changes with it (the BF16 and FP8_E4M3 sizes just named
+ * ran direct tiles before the rule packed them).  Each call writes every byte
+ * of the region it reads before reading it, so no clearing is needed.
  */
 int tgemm_noalloc(int64_t M, int64_t N, int64_t K, float alpha,
                   const void* A, int64_t lda, const void* B, int64_t ldb,
@@ -201,8 +209,10 @@ int tgemm_batched(int64_t count, const int64_t* M, const int64_t* N, const int64
  * tgemm: batch, H, W or Cout == 0 is a no-op; Cin == 0 or alpha == 0 gives
  * Y = beta*Y without reading X or Wt; beta == 0 does not read Y.
  * Kernel: the packed one (TGEMM_CONV_PACKED below) when X spans fewer than
- * 2^31 bytes (x3: 2^30 elements), else the direct one; under stream capture
- * with a workspace too small, the direct one.  Packed tile shape: 0 for f32;
+ * 2^31 bytes (x3: 2^30 elements), else the direct one; the direct one, too, for
+ * f32 layers of fewer than 128 tiles of 128 x 128 (M = batch*H*W, Cout a
+ * multiple of 4), and under stream capture with a workspace too small.  Packed
+ * tile shape: 0 for f32;
  * for x3, 1 (256 x 256) when Cout >= 256 and ceil(M/256)*ceil(Cout/256) >=
  * 256 with M = batch*H*W, else 0.
  */
@@ -221,8 +231,8 @@ int tgemm_conv3x3(int64_t batch, int64_t H, int64_t W, int64_t Cin, int64_t Cout
  *   E = alpha * T D + beta * E  D: N1 x N2 (ldd), E: M x N2 (lde)
  * act: TGEMM_ACT_NONE or TGEMM_ACT_RELU (max(x, 0), NaN kept).  All matrices
  * row-major float, DEVICE pointers, any alignment.  T is formed in FP32, 64
- * rows at a time, in LDS and never written to memory.  dtype: TGEMM_F32 or
- * TGEMM_F32_BF16X3 (the x3 form of both products; T is split like any
+ * or 32 rows at a time, in LDS and never written to memory.  dtype: TGEMM_F32
+ * or TGEMM_F32_BF16X3 (the x3 form of both products; T is split like any
  * operand).  N1 <= 256, and 64*lda*4, 16*ldb*4 and 16*ldd*4 below 2^31, else
  * TGEMM_NOT_SUPPORTED; lda < K, ldb < N1, ldd < N2 or lde < N2 give
  * TGEMM_INVALID_VALUE.  Degenerate cases as for tgemm: M or N2 == 0 is a no-op;
@@ -243,8 +253,11 @@ int tgemm_gemm2(int64_t M, int64_t N1, int64_t N2, int64_t K, float alpha, const
  * arrays).  A mode in A, B and C is a batch mode, in A and C a row mode, in
  * B and C a column mode, in A and B a contracted mode.  The contraction runs
  * as a batch of row x contracted by contracted x column gemms (tgemm for one,
- * tgemm_batched_strided for several; dtype TGEMM_F32 or TGEMM_F32_BF16X3); an
- * operand not already laid out [batch, row, contracted] ([batch, contracted,
+ * tgemm_batched_strided for several; dtype TGEMM_F32 or TGEMM_F32_BF16X3).
+ * Where the batch, row, column and contracted modes of each tensor run at one
+ * stride and register tiles pay, these read the operands in place, with neither
+ * copies nor a plan (so also under stream capture).  Otherwise an operand not
+ * already laid out [batch, row, contracted] ([batch, contracted,
  * column] for B, [batch, row, column] for C; batch, row and column modes in
  * C's order, contracted modes in A's) is first copied into that order in a
  * per-(device, stream) workspace the library owns (not grown under stream
@@ -345,9 +358,12 @@ int tgemm_batched_with_shape(int64_t count, const int64_t* M, const int64_t* N, 
  * The plan is cached under these 17 scalars, so a repeated call costs
  * constant host time whatever the count (tgemm_batched hashes every
  * problem's arguments).  Problems with M and N at most 32 skip the plan: one
- * wave per problem multiplies from registers with FP32 MFMAs (both dtypes).  Problems' C blocks must not overlap (strideC >=
- * (M-1)*ldc + N when count > 1) and strides must be >= 0, else
- * TGEMM_INVALID_VALUE; otherwise as tgemm_batched.
+ * wave per problem multiplies from registers with FP32 MFMAs (both dtypes).
+ * So do batches of few tiles (up to 1100 of 64 x 64; 256 with K below 128), on
+ * register tiles.  Neither is touched by tgemm_batched_autotune or refused under
+ * stream capture.  Problems' C blocks must not overlap (strideC >= (M-1)*ldc + N
+ * when count > 1) and strides must be >= 0, else TGEMM_INVALID_VALUE; otherwise
+ * as tgemm_batched.
  */
 int tgemm_batched_strided(int64_t count, int64_t M, int64_t N, int64_t K, float alpha, const void* A,
                           int64_t lda, int64_t strideA, const void* B, int64_t ldb, int64_t strideB,
@@ -457,9 +473,13 @@ uint64_t tgemm_schedule_space_hash(void);
 /* Schedule the current policy would pick for a dense problem (row strides K
  * and N, 16-byte aligned bases).  Under the built-in rule tgemm and
  * tgemm_noalloc run float32 problems of few tiles on register tiles, which are
- * no schedules of the table; what is reported here is the schedule that serves
- * such a problem where those tiles do not (operands off 4-byte alignment or
- * row strides past their reach).  Host-only. */
+ * no schedules of the table, and in-place 64 x 64 tiles of float32 joined to
+ * 128 x 128 where these are more than 256 and at most 192 past a multiple of
+ * 256 (the same sums; those past it run as quarters).  What is reported here is
+ * the schedule that serves such a problem where those forms do not (operands off
+ * 4-byte alignment or row strides past their reach).  The "tuned", "model" and
+ * "force" policies name schedules of the table and run what they name.
+ * Host-only. */
 int tgemm_select_schedule(int64_t M, int64_t N, int64_t K, int dtype,
                           int* schedule_id, int* group_m, int* xcd_remap);
 
@@ -472,7 +492,9 @@ int tgemm_select_schedule(int64_t M, int64_t N, int64_t K, int dtype,
  * layer: W_l (dims[l] x dims[l+1], row-major) then b_l.  X is rows x dims[0]
  * row-major on the device; y and out have `rows` entries.  `work` is a device
  * scratch buffer of tgemm_mlp_workspace_count() floats owned by the caller.
- * Matrix products run on this library's F32 gemm (built-in schedule rule).
+ * Matrix products run on this library's F32 gemm (built-in schedule rule), or,
+ * in networks of few tiles, on its register tiles with the element-wise steps in
+ * their epilogues.
  */
 int64_t tgemm_mlp_param_count(int layers, const int* dims);
 int64_t tgemm_mlp_workspace_count(int layers, const int* dims, int64_t rows);

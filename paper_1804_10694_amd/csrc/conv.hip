@@ -398,9 +398,12 @@ const ConvPacked kConvPacked[] = {
 };
 
 // f32 layers of fewer than 128 tiles of 128 x 128 leave half of the CUs idle in the
-// packed kernel: the direct one on 64 x 64 tiles takes 0.52 to 0.77 of its time there (52
-// tiles, 8 x 14 x 14 x 512 -> 512, 351 us / 197; 98, 8 x 28 x 28 x 256 -> 256, 179 / 136), 1.23
-// at 196.  x3 gains less than the 8% it loses elsewhere (126 / 136, 71 / 67).
+// packed kernel.  Time of the direct one on 64 x 64 tiles against it, 18 layers of 2 to
+// 124 tiles: 1 x 1 filters 0.47 to 0.78, 3 x 3 0.49 to 0.79, 5 x 5 0.55 to 0.83, 7 x 7
+// 0.56 to 0.83 (52 tiles, 8 x 14 x 14 x 512 -> 512, 3 x 3 192 us / 351; 124, 10 x 28 x 28 x
+// 256 -> 256, 136 / 180), and the same with filters off 16-byte alignment.  Past the line,
+// 148 tiles: 0.81, 0.97, 1.06, 1.08; 196: 0.86, 1.19, 1.36, 1.39.  x3 gains less than the
+// 8% it loses elsewhere (126 / 136, 71 / 67).
 bool conv_few_tiles(int dtype, int64_t M, int64_t Cout)
 {
     return dtype == TGEMM_F32 && Cout % 4 == 0 && ((M + 127) / 128) * ((Cout + 127) / 128) < 128;

@@ -843,7 +843,9 @@ extern "C" int tgemm_noalloc(int64_t M, int64_t N, int64_t K, float alpha, const
         return run_scaled(M, N, K, alpha, A, lda, nullptr, B, ldb, nullptr, beta, C, ldc, dtype, ch.id, ch.group_m,
                           ch.xcd_remap, s);
     }
-    if (ch.reg >= 0 && reg_serves(A, true, lda, B, false, ldb))  // few tiles: no workspace after all
+    // few tiles: no workspace after all (after the limits, so that what they refuse does
+    // not depend on the operands' alignment and strides)
+    if (ch.reg >= 0 && reg_serves(A, true, lda, B, false, ldb))
         return run_choice(ch, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, dtype, s);
     void* ws = nullptr;
     if ((rc = scratch_address(&ws)) != TGEMM_SUCCESS) return rc;

@@ -32,9 +32,9 @@ const SchedDesc* tile_schedules(int* n);    // F32 and split-bf16x3
 const SchedDesc* scaled_schedules(int* n);  // bf16 and fp8 with per-tile scales
 const SchedDesc* packed_schedules(int* n);  // packed-operand f32, x3, bf16, fp8
 const SchedDesc* inplace_schedules(int* n); // in-place f32 and x3 (gemm_inplace.hip)
+bool inplace_joined(int64_t M, int64_t N);  // f32: 64 x 64 tiles run joined to 128 x 128
 // Whether an in-place schedule reaches every row it loads with 32-bit buffer
 // offsets for these row strides.
-bool inplace_joined(int64_t M, int64_t N);  // f32: 64 x 64 tiles run joined to 128 x 128
 bool inplace_reach_ok(const SchedDesc& d, int64_t lda, int64_t ldb);
 
 // Packed schedules (gemm_packed.hip): index within packed_schedules().

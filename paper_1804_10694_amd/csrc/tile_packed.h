@@ -961,8 +961,9 @@ __device__ __forceinline__ int packed_tile_range(const PackedArgs& a, int m0, in
     // block (128 deep).  The products of the next block are loaded one panel
     // ahead, before that panel's successor is issued, so the waits of the panel
     // pipeline cover them; loading them where they are used would drain the
-    // panels in flight at every block boundary.  (They are vector loads: C is
-    // written by the same kernel and may alias the scales.)
+    // panels in flight at every block boundary.  (They are vector loads, counted with
+    // the panels'; the tiles that take turns read them as scalars.  Scales do not
+    // change during the kernel: they must not overlap C.)
     // A wave tile no larger than a 128 x 128 scale tile lies inside one (tiles
     // start at multiples of their size), so one product serves all its blocks.
     static_assert(!scaled || (CF::WTM <= 128 && CF::WTN <= 128), "one scale product per wave");
