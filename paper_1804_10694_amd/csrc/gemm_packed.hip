@@ -83,7 +83,7 @@ __global__ void __launch_bounds__(256) step_cols_kernel(const void* X, int64_t l
     step_col_block<MODE>(X, ldx, K, N, P, Kp, blockIdx.x * 64, blockIdx.y * 64, tile, vec != 0);
 }
 
-template <class CF>
+template <class CF, bool SCALES = true>
 __global__ void __launch_bounds__(CF::NT, CF::WAVES_PER_EU) packed_kernel(PackedArgs a)
 {
     static_assert(kPackK % CF::BK == 0 && CF::BM <= kPackRows && CF::BN <= kPackRows &&
@@ -91,7 +91,8 @@ __global__ void __launch_bounds__(CF::NT, CF::WAVES_PER_EU) packed_kernel(Packed
                   "tiles and panels divide the packing padding");
     __shared__ __attribute__((aligned(1024))) char lds[CF::LDS_BYTES];
     const TileCoord tc = map_tile(blockIdx.x, a.tiles_m, a.tiles_n, a.group_m, a.xcd_remap);
-    packed_tile<CF>(a, tc.tm * CF::BM, tc.tn * CF::BN, lds);
+    packed_tile<CF, typename TileParts<CF>::A, typename TileParts<CF>::B, typename TileParts<CF>::Op, SCALES>(
+        a, tc.tm * CF::BM, tc.tn * CF::BN, lds);
 }
 
 // Stream-K: one resident wave of `grid` workgroups.  Each first computes the
@@ -329,6 +330,7 @@ struct PSched {
     void (*sk_kernel)(PackedArgs, SkArgs);  // stream-K form, or null
     int mfma;                               // MFMA block (32 or 16)
     int step = 0;                           // k per step of step-packed operands (0: row-packed)
+    void (*folded)(PackedArgs) = nullptr;   // see folded()
 };
 
 #define TG_PSCHED(DT, MODE, BM, BN, BK, WGM, WGN, NS)                                             \
@@ -357,6 +359,17 @@ constexpr PSched turns(int dtype, int BK)
     return {dtype, MODE, BM, BN, BK, WGM, WGN, CF::LDS_BYTES, CF::NT, &packed_kernel<CF>, sk, MS, CF::BK};
 }
 
+// A bf16 schedule whose K blocks are summed by themselves (FCfg) with scales, and
+// without them below many_deep_tiles: there direct tiles, which sum so, were the rule's
+// choice before packed ones, and results are no further off than theirs.
+template <int BM, int BN, int BK, int WGM, int WGN, int MS>
+constexpr PSched folded()
+{
+    using CF = PCfg<MODE_BF16, BM, BN, BK, WGM, WGN, 2, MS>;
+    return {TGEMM_BF16, MODE_BF16, BM, BN, BK, WGM, WGN, CF::LDS_BYTES, CF::NT, &packed_kernel<CF, false>,
+            nullptr, MS, 0, &packed_kernel<FCfg<BM, BN, BK, WGM, WGN, 2, MS>>};
+}
+
 constexpr PSched kPacked[] = {
     // two workgroups per CU (LDS <= 80 KB), 4 waves each
     TG_PSCHED(TGEMM_F32, MODE_F32, 128, 128, 32, 2, 2, 2),
@@ -381,7 +394,7 @@ constexpr PSched kPacked[] = {
     TG_PSCHED(TGEMM_F32_BF16X3, MODE_X3, 128, 128, 32, 2, 2, 2),
     TG_PSCHED_SK(TGEMM_BF16, MODE_BF16, 256, 256, 64, 2, 4, 2),
     TG_PSCHED(TGEMM_BF16, MODE_BF16, 256, 256, 32, 2, 4, 4),
-    TG_PSCHED(TGEMM_BF16, MODE_BF16, 128, 128, 64, 2, 2, 2),
+    folded<128, 128, 64, 2, 2, 32>(),
     turns<MODE_FP8, 256, 256, 2, 4, 32, false>(TGEMM_FP8_E4M3, 128),
     turns<MODE_FP8, 256, 256, 4, 2, 32, true>(TGEMM_FP8_E4M3, 128),
     TG_PSCHED(TGEMM_FP8_E4M3, MODE_FP8, 256, 256, 64, 2, 4, 4),
@@ -393,7 +406,7 @@ constexpr PSched kPacked[] = {
     TG_PSCHED16(TGEMM_F32_BF16X3, MODE_X3, 128, 128, 32, 2, 2, 2),
     TG_PSCHED16(TGEMM_F32_BF16X3, MODE_X3, 256, 128, 32, 2, 4, 3),
     TG_PSCHED16(TGEMM_BF16, MODE_BF16, 256, 256, 64, 2, 4, 2),
-    TG_PSCHED16(TGEMM_BF16, MODE_BF16, 128, 128, 64, 2, 2, 2),
+    folded<128, 128, 64, 2, 2, 16>(),
     TG_PSCHED16(TGEMM_FP8_E4M3, MODE_FP8, 256, 256, 128, 4, 2, 2),
     TG_PSCHED16(TGEMM_FP8_E4M3, MODE_FP8, 128, 128, 128, 2, 2, 2),
 };
@@ -753,7 +766,9 @@ int run_packed_ws(int pid, int64_t M, int64_t N, int64_t K, float alpha, const v
         a.group_m = group_m < 1 ? 1 : group_m;
         hipLaunchKernelGGL(p.sk_kernel, dim3((unsigned)grid), dim3(p.threads), 0, s, a, k);
     } else {
-        hipLaunchKernelGGL(p.kernel, dim3((unsigned)tiles), dim3(p.threads), 0, s, a);
+        const bool folded = p.folded && (sA || !many_deep_tiles(M, N, K));
+        void (*kernel)(PackedArgs) = folded ? p.folded : p.kernel;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(p.threads), 0, s, a);
     }
     return hipGetLastError() == hipSuccess ? TGEMM_SUCCESS : TGEMM_LAUNCH_FAILED;
 }

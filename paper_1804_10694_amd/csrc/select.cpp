@@ -321,13 +321,18 @@ static int table_rule(int64_t M, int64_t N, int64_t K, int dtype, bool vec_allow
     return direct_schedule(M, N, K, dtype, vec_allowed, out);
 }
 
+bool many_deep_tiles(int64_t M, int64_t N, int64_t K)
+{
+    auto tiles = [&](int b) { return ((M + b - 1) / b) * ((N + b - 1) / b); };
+    return K >= 512 && (tiles(256) >= 128 || tiles(128) >= 192);
+}
+
 // Large and deep sizes must have the workspace; so must a schedule that a policy
 // names (forced, tuned or predicted).
 bool packing_optional(int id, int64_t M, int64_t N, int64_t K, int dtype, bool vec_allowed)
 {
     if (dtype != TGEMM_BF16 && dtype != TGEMM_FP8_E4M3) return false;
-    auto tiles = [&](int b) { return ((M + b - 1) / b) * ((N + b - 1) / b); };
-    if (K >= 512 && (tiles(256) >= 128 || tiles(128) >= 192)) return false;
+    if (many_deep_tiles(M, N, K)) return false;
     Choice rule;
     return default_schedule(M, N, K, dtype, vec_allowed, &rule) == TGEMM_SUCCESS && rule.id == id;
 }

@@ -34,6 +34,10 @@ bool costmodel_cached(int64_t M, int64_t N, int64_t K, int dtype, bool vec_allow
 // Built-in rule only (also the fallback of the other policies).
 int default_schedule(int64_t M, int64_t N, int64_t K, int dtype, bool vec_allowed, Choice* out);
 
+// bf16 and e4m3 sizes of many tiles and deep K, where packed tiles are the only ones
+// near the matrix cores' rate.
+bool many_deep_tiles(int64_t M, int64_t N, int64_t K);
+
 // bf16 and e4m3: whether `id` is the packed schedule that the built-in rule names for a
 // problem that direct tiles serve as well where no workspace can be had.
 bool packing_optional(int id, int64_t M, int64_t N, int64_t K, int dtype, bool vec_allowed);

@@ -47,7 +47,7 @@ struct ICfg {
     static constexpr int NG = BK / MK;
     static constexpr int WTM = BM / WGM, WTN = BN / WGN, TM = WTM / 32, TN = WTN / 32;
     static constexpr int MS = 32, AR = 16;                     // 32 x 32 MFMA blocks
-    static constexpr bool TURNS = false;
+    static constexpr bool TURNS = false, FOLD = false;
     using Acc = f32x16;
     __device__ __forceinline__ static int out_row(int r, int lane) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); }
     __device__ __forceinline__ static int out_col(int lane) { return lane & 31; }

@@ -234,7 +234,7 @@ struct PCfg {
     static constexpr int MODE = MODE_, BM = BM_, BN = BN_, BK = BK_, WGM = WGM_, WGN = WGN_;
     static constexpr int NS = NS_;  // LDS stages (panels in flight = NS - 1)
     static constexpr int MS = MS_;
-    static constexpr bool TURNS = false;                 // see TCfg
+    static constexpr bool TURNS = false, FOLD = false;   // see TCfg, FCfg
     static constexpr int LG = 64 / MS;                   // lane groups along k of one MFMA
     static constexpr int AR = MS * MS / 64;              // accumulator registers per lane per block
     using Acc = typename std::conditional<MS == 32, f32x16, f32x4>::type;
@@ -285,6 +285,19 @@ template <int MODE_, int BM_, int BN_, int WGM_, int WGN_, int NS_, int MS_ = 32
 struct TCfg : PCfg<MODE_, BM_, BN_, MODE_ == MODE_FP8 ? 64 : 16, WGM_, WGN_, NS_, MS_> {
     static constexpr bool TURNS = true;
     static_assert(WGM_ * WGN_ == 8 && (MODE_ == MODE_X3 || MODE_ == MODE_FP8), "two waves per SIMD, x3 or e4m3");
+};
+
+// bf16 tiles that sum each K block of 128 by itself and add it, scaled, to the whole
+// (two sets of accumulators), as the direct tiles do: one running float32 sum over
+// 16384 k is off by 7.9e-7, this by 2.4e-7 (300 x 300; 4096 k: 4.2e-7 and 1.4e-7).
+// With scales it is also the faster one, since a running sum has to be moved to every
+// new scale product (2048 x 4096 x 4096 97.3 -> 94.7 us, 2500^2 x 8192 167.8 -> 158.9);
+// without, it adds 64 vector instructions per 32 MFMAs of a wave (1000^3 22.9 -> 23.5 us,
+// 33 x 2451 x 5760 80.5 -> 82.1).
+template <int BM_, int BN_, int BK_, int WGM_, int WGN_, int NS_, int MS_>
+struct FCfg : PCfg<MODE_BF16, BM_, BN_, BK_, WGM_, WGN_, NS_, MS_> {
+    static constexpr bool FOLD = true;
+    static_assert(NS_ == 2 && (BM_ < 256 || BN_ < 256) && 128 % BK_ == 0, "the two-stage loop of smaller tiles");
 };
 
 // Step-packed operands.  A step holds four units of a row: 64 k (e4m3), or
@@ -877,9 +890,9 @@ static_assert(same_unit_range(127, 151) && !same_unit_range(127, 152) && !same_u
 // from it they would overflow or vanish beside sums that float32 holds (2^116, then
 // 2^-80, gave NaN), so they stay within 2^24 of the product they began with; the
 // next K block begins new ones.  One wave looks, 64 K blocks at a time, while the
-// tile's first panels are on their way: 2048 x 4096 x 4096 98.8 -> 99.9 us, 1000^3
-// 24.7 -> 25.2, 5000^2 x 300 49.8 -> 52.  (The caller's loop over the runs is apart
-// from the first of them: in one loop its state cost the main loop another 2 to 4%.)
+// tile's first panels are on their way: 5000^2 x 300 49.8 -> 52 us, stream-K 300 x 3000
+// x 8000 103.6 -> 104.2.  (The caller's loop over the runs is apart from the first of
+// them: in one loop its state cost the main loop another 2 to 4%.)
 // `word` is a part of the panels' LDS that none of them goes to, free again after the
 // next barrier (a second LDS object in the kernel makes the compiler wait for every
 // panel load in flight before each LDS read: 1.4 times the time).
@@ -999,7 +1012,7 @@ __device__ __forceinline__ int packed_tile_range(const PackedArgs& a, int m0, in
     constexpr int NS = CF::NS, L = AL::LOADS + BL::LOADS;
     static_assert((NS - 2) * L <= 63, "vmcnt holds at most 63");
     for (int p = 0; p < NS - 1 && p < np; ++p) issue(p, lds + p * CF::LDS_STAGE);
-    constexpr bool runs = scaled && !mx;
+    constexpr bool runs = scaled && !mx && !CF::FOLD;
     const int npanel = [&] {
         if constexpr (runs)
             return unit_run<CF>(a, m0, n0, p0, np, reinterpret_cast<int*>(lds + (NS - 1) * CF::LDS_STAGE));
@@ -1071,6 +1084,49 @@ __device__ __forceinline__ int packed_tile_range(const PackedArgs& a, int m0, in
         sc_cur = sc_next;
         kb_cur = kb;
     };
+    if constexpr (CF::FOLD) {
+        // acc holds one K block's sums, tot the whole in true units.  The loop is the
+        // two-stage one below; a panel that opens a K block (p0 is 0) adds the last one's
+        // sums first and starts from a constant.
+        typename CF::Acc tot[CF::TM][CF::TN];
+        auto each = [&](const auto& f) {
+#pragma unroll
+            for (int i = 0; i < CF::TM; ++i)
+#pragma unroll
+                for (int j = 0; j < CF::TN; ++j)
+#pragma unroll
+                    for (int r = 0; r < CF::AR; ++r) f(tot[i][j], acc[i][j], r);
+        };
+        each([](typename CF::Acc& t, typename CF::Acc&, int r) { t[r] = 0.f; });
+        auto fold = [&] {
+            const float f = scaled ? sc_cur : 1.f;
+            each([&](typename CF::Acc& t, typename CF::Acc& x, int r) { t[r] = fmaf(f, x[r], t[r]); });
+        };
+        for (int s = 0; s < npanel; ++s) {
+            wait_vmcnt<0>();
+            lds_barrier();
+            const char* stage = lds + (s & 1) * CF::LDS_STAGE;
+            auto next = [&] {
+                prefetch(s);
+                if (s + 1 < npanel) issue(s + 1, lds + ((s + 1) & 1) * CF::LDS_STAGE);
+            };
+            if (s % (128 / CF::BK) == 0) {
+                if (s > 0) {
+                    fold();
+                    sc_cur = sc_next;
+                }
+                next();
+                each([](typename CF::Acc&, typename CF::Acc& x, int r) { x[r] = 0.f; });
+                pk_mma<CF, OP>(stage, acc, wm0, wn0, lane);
+            } else {
+                next();
+                pk_mma<CF, OP>(stage, acc, wm0, wn0, lane);
+            }
+        }
+        fold();
+        epi(tot, [](int, int) { return 1.f; }, wm0, wn0, lane, false);
+        return npanel;
+    }
     if constexpr (CF::TURNS) {
         // Two groups of four waves, one wave of each on every SIMD, take turns:
         // in each slot one group reads a step's operands from LDS (and issues
@@ -1237,13 +1293,14 @@ __device__ __forceinline__ int packed_tile_range(const PackedArgs& a, int m0, in
 }
 
 // One whole macro-tile (all K panels) with the standard epilogue.
+// SCALES: whether the problem may have scales (bf16 and e4m3).
 template <class CF, class AL = typename TileParts<CF>::A, class BL = typename TileParts<CF>::B,
-          class OP = typename TileParts<CF>::Op>
+          class OP = typename TileParts<CF>::Op, bool SCALES = true>
 __device__ __forceinline__ void packed_tile(const PackedArgs& a, int m0, int n0, char* lds,
                                             const typename AL::Geom& geom = typename AL::Geom())
 {
     const int np = (a.K + CF::BK - 1) / CF::BK;
-    if constexpr (CF::MODE == MODE_BF16)
+    if constexpr (CF::MODE == MODE_BF16 && SCALES && !CF::FOLD)
         if (a.sA) {
             int p = packed_tile_range<CF, AL, BL, OP, true>(a, m0, n0, lds, geom, 0, np, TileStore<CF>{a, m0, n0});
             while (__builtin_expect(p < np, 0)) {  // sums in other units
@@ -1253,7 +1310,7 @@ __device__ __forceinline__ void packed_tile(const PackedArgs& a, int m0, int n0,
             }
             return;
         }
-    if (CF::MODE == MODE_FP8 && a.sA)
+    if ((CF::MODE == MODE_FP8 || CF::FOLD) && a.sA)
         packed_tile_range<CF, AL, BL, OP, true>(a, m0, n0, lds, geom, 0, np, TileStore<CF>{a, m0, n0});
     else
         packed_tile_range<CF, AL, BL, OP, false>(a, m0, n0, lds, geom, 0, np, TileStore<CF>{a, m0, n0});
